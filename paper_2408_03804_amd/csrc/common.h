@@ -63,7 +63,16 @@ struct AxisPlan {
   const double2* tw;
   const double2* chirp;  // chirp-z axes only
   const double2* filt;   // chirp-z axes only
+  int dense;             // the transform is a folded dense DFT on the matrix cores (see fft_dense)
+  const double2* frag;   // dense axes only: (cos, sin) operand fragments, dense_elems(n) entries
 };
+
+// Folded dense DFT of length n (n >= 17): output rows k = 0..n/2 in tiles of 16, folded inputs
+// t = 1..n/2 in matrix-core steps of 4 (rounded up to a multiple of 4 steps).
+__host__ __device__ inline int dense_rows(int n) { return n / 2 / 16 + 1; }
+__host__ __device__ inline int dense_steps(int n) { return (n / 2 + 15) / 16 * 4; }
+constexpr int kDenseCols = 8;  // complex sequences per column tile (16 real columns)
+constexpr int kDenseHold = 2;  // tiles a wavefront holds in registers for the in-place transform
 
 // Rows per sequence that a transform of this axis occupies in LDS.
 __host__ __device__ inline int lds_len(const AxisPlan& p) { return p.m > 0 ? p.m : p.n; }

@@ -48,7 +48,7 @@ struct Layout {
   size_t n_results;
   int in_x, in_m, in_o;  // in-place (register-staged) FFT per pass
   size_t n_partials, smem_max;
-  bool chirp;  // axes with large prime factors use the chirp-z transform (else direct stages)
+  int plans;  // which transforms the axes may take (PlanSet)
 };
 
 // Chirp-z thresholds (sum of the direct stages' prime lengths above 5, see make_plan), measured per
@@ -60,11 +60,18 @@ struct Layout {
 constexpr int kChirpOuter = 70;
 constexpr int kChirpRows = 150;
 
+// Transforms the axes of a layout may take: radix and direct prime stages only, also the chirp-z
+// form, also the folded dense DFT.
+enum PlanSet { PLANS_DIRECT = 0, PLANS_CHIRP = 1, PLANS_DENSE = 2 };
+
 // FFT plans of the axes of d (pl[2] = pl[1] in 2D) and the LDS lengths of g that follow from them.
-bool make_plans(const fft_homog_desc* d, bool chirp, AxisPlan* pl, Geom* g) {
+bool make_plans(const fft_homog_desc* d, int plans, AxisPlan* pl, Geom* g) {
   for (int a = 0; a < 3; ++a) {
-    const int lim = !chirp ? 0 : a == d->ndim - 1 ? kChirpOuter : kChirpRows;
-    if (!make_plan(a < d->ndim ? d->n[a] : 1, &pl[a], lim)) return false;
+    const int n = a < d->ndim ? d->n[a] : 1;
+    const bool dense = plans >= PLANS_DENSE && dense_len(n);
+    const int lim = plans < PLANS_CHIRP || dense ? 0 : a == d->ndim - 1 ? kChirpOuter : kChirpRows;
+    if (!make_plan(n, &pl[a], lim)) return false;
+    pl[a].dense = dense ? 1 : 0;
   }
   if (d->ndim == 2) pl[2] = pl[1];
   set_lds_lens(g, pl);
@@ -153,13 +160,13 @@ size_t smem_needed(const Geom& g, const AxisPlan* pl, const Layout& L) {
   return m;
 }
 
-int make_layout_with(const fft_homog_desc* d, Layout* L, bool chirp) {
+int make_layout_with(const fft_homog_desc* d, Layout* L, int plans) {
   Geom g;
   make_geom(d, &g);
   const int C = g.c;
   AxisPlan pl[3];
-  if (!make_plans(d, chirp, pl, &g)) return FFT_HOMOG_EUNSUPPORTED;
-  L->chirp = chirp;
+  if (!make_plans(d, plans, pl, &g)) return FFT_HOMOG_EUNSUPPORTED;
+  L->plans = plans;
   L->cells = d->batch > 1 ? d->batch : 1;
   L->B = (d->flags & FFT_HOMOG_FLAG_TANGENT) ? C * L->cells : 1;
   const AxisPlan& pouter = pl[d->ndim - 1];
@@ -265,12 +272,15 @@ int make_layout_with(const fft_homog_desc* d, Layout* L, bool chirp) {
   return FFT_HOMOG_OK;
 }
 
-// Chirp-z plans where they cost less; the direct stages if the chirp-z buffers do not fit LDS.
-int make_layout(const fft_homog_desc* d, Layout* L) {
-  const int rc = validate_desc(d);
+// The dense DFT and chirp-z plans where they cost less; fewer of them if their buffers do not fit LDS.
+int make_layout(const fft_homog_desc* d, Layout* L, int plans = PLANS_DENSE) {
+  int rc = validate_desc(d);
   if (rc) return rc;
-  if (make_layout_with(d, L, true) == FFT_HOMOG_OK) return FFT_HOMOG_OK;
-  return make_layout_with(d, L, false);
+  for (; plans >= PLANS_DIRECT; --plans) {
+    rc = make_layout_with(d, L, plans);
+    if (rc == FFT_HOMOG_OK) break;
+  }
+  return rc;
 }
 
 // out = G*in for `batch` packed fields: the x pass (real-to-complex), the y pass, the outer pass
@@ -800,7 +810,7 @@ int fft_homog_create(const fft_homog_desc* d, void* dev_workspace, size_t bytes,
   fft_homog_t* h = new fft_homog();
   h->desc = *d;
   make_geom(d, &h->g);
-  make_plans(d, L.chirp, h->plan, &h->g);
+  make_plans(d, L.plans, h->plan, &h->g);
   h->L = L;
   h->matcode = material_code(d);
   h->stream = (hipStream_t)hip_stream;
@@ -1635,21 +1645,26 @@ int fft_homog_tune_placement(fft_homog_t* h, int reps, size_t* stagger) {
 int fft_homog_project_noalloc(const fft_homog_desc* d, const double* in, double* out, int batch, void* hip_stream) {
   if (!in || !out || batch < 1) return create_fail(FFT_HOMOG_EINVAL, "null field or batch < 1", hipSuccess);
   Layout L;
-  const int rc = make_layout(d, &L);
-  if (rc) return create_fail(rc, "invalid or unsupported descriptor", hipSuccess);
   Geom g;
-  make_geom(d, &g);
   AxisPlan pl[3];
-  make_plans(d, L.chirp, pl, &g);
-  // scratch: FFT tables of the axes, then the half spectrum [batch][c][z][y][pitch]
-  size_t off = 0;
   size_t tw_off[3] = {0, 0, 0};
-  for (int a = 0; a < d->ndim; ++a) {
-    tw_off[a] = off;
-    off = align_up(off + plan_table_elems(pl[a]) * sizeof(double2));
+  size_t spec_off = 0, need = 0;
+  // scratch: FFT tables of the axes, then the half spectrum [batch][c][z][y][pitch]; a request that
+  // only the dense DFT's tables push beyond the scratch runs without it
+  for (int plans = PLANS_DENSE; plans >= PLANS_CHIRP; --plans) {
+    const int rc = make_layout(d, &L, plans);
+    if (rc) return create_fail(rc, "invalid or unsupported descriptor", hipSuccess);
+    make_geom(d, &g);
+    make_plans(d, L.plans, pl, &g);
+    size_t off = 0;
+    for (int a = 0; a < d->ndim; ++a) {
+      tw_off[a] = off;
+      off = align_up(off + plan_table_elems(pl[a]) * sizeof(double2));
+    }
+    spec_off = off;
+    need = spec_off + (size_t)batch * g.c * g.Nh * sizeof(double2);
+    if (need <= kNoAllocScratchBytes) break;
   }
-  const size_t spec_off = off;
-  const size_t need = spec_off + (size_t)batch * g.c * g.Nh * sizeof(double2);
   if (need > kNoAllocScratchBytes) {
     char msg[160];
     snprintf(msg, sizeof(msg), "needs %zu bytes of scratch; the allocation-free projection has %zu per device",

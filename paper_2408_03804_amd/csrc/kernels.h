@@ -97,11 +97,21 @@ bool inplace_ok(const AxisPlan& pl, int nseq);
 // length when the direct stages' prime lengths other than 2, 3 and 5 sum to more than chirp_above
 // (0: never); table pointers left null.  False if n has no factorisation within kMaxStages stages.
 bool make_plan(int n, AxisPlan* pl, int chirp_above);
+// true if an axis of length n runs the folded dense DFT: every length without a compiled schedule from
+// 17 (below, one row tile would be mostly padding) to kDenseMax points.  Measured against the radix,
+// direct prime and chirp-z stages it replaces: a CG iteration's passes at 199 points (prime) 26 + 40 +
+// 24 us -> 14 + 23 + 13 us, at 33^3 20 + 15 + 20 us (y, outer, y) -> 13 + 9 + 13 us; its cost per
+// element grows with n, and at 299 = 13 * 23 points the direct stages were faster (25 against 29 ms
+// per solve).
+constexpr int kDenseMax = 256;
+bool dense_len(int n);
+size_t dense_elems(int n);  // entries of its operand-fragment table
 // LDS rows per sequence of the x, mid and outer transforms of the plans pl[0..ndim-1]
 void set_lds_lens(Geom* g, const AxisPlan* pl);
 // the stages of length n (radices 16/8/4/2/3/5 and remaining primes); false if more than kMaxStages
 bool factorize(int n, int* radix, int* nst);
 // complex entries of an axis plan's device tables: twiddles of lds_len, then chirp (n) and filter (m)
+// of a chirp-z axis, or the operand fragments of a dense axis
 size_t plan_table_elems(const AxisPlan& pl);
 // set the table pointers of pl into `base` (plan_table_elems entries, device memory) and fill the
 // tables: the twiddles (exp(-2 pi i j / L) by sincospi of exact rational arguments) unless the
@@ -147,21 +157,34 @@ hipError_t launch_simp_gradient(int mat, const double* F, const double* x, MatPa
 hipError_t launch_j2_commit(int mat, const double* F, MatParams m, double* hist, const Geom& g, hipStream_t s);
 hipError_t launch_j2_plastic(int mat, const double* F, MatParams m, double* out, const Geom& g, hipStream_t s);
 hipError_t set_smem_limits(const Geom& g, int mat, size_t bytes);
+// forward x pass of one law with FFT variant nf (pass_fft in pass_kernels.h); dynamic-LDS limits
+#define FH_XPASS_DECL(name)                                                                                  \
+  hipError_t name(int nf, int prod, int mat, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s); \
+  hipError_t name##_limits(int mat, size_t bytes);
+FH_XPASS_DECL(xfwd_le)
+FH_XPASS_DECL(xfwd_nh)
+FH_XPASS_DECL(xfwd_stvk)
+FH_XPASS_DECL(xfwd_j2)
+FH_XPASS_DECL(xfwd_ps)
+#undef FH_XPASS_DECL
 // the pass kernels with the chirp-z transform (kernels_chirp.hip), for plans with m > 0
-hipError_t launch_xfwd_chirp(int prod, int mat, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s);
 hipError_t launch_xinv_chirp(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s);
 hipError_t launch_mid_chirp(int dir, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s);
 hipError_t launch_outer_chirp(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s);
-hipError_t set_smem_limits_chirp(const Geom& g, int mat, size_t bytes);
+hipError_t set_smem_limits_chirp(const Geom& g, size_t bytes);
+// the pass kernels with the folded dense DFT (kernels_dense.hip), for plans with dense set
+hipError_t launch_xinv_dense(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s);
+hipError_t launch_mid_dense(int dir, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s);
+hipError_t launch_outer_dense(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s);
+hipError_t set_smem_limits_dense(const Geom& g, size_t bytes);
 // the CG-loop pass kernels for single axis lengths with compiled schedules (kernels_fixed.hip):
 // lengths that have them; each launcher sets *done when it launched (else the caller launches the
 // generic kernel)
 bool fixed_len_kernels(int n);
-hipError_t launch_xfwd_fixed(int prod, int mat, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done);
 hipError_t launch_xinv_fixed(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done);
 hipError_t launch_mid_fixed(int dir, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done);
 hipError_t launch_outer_fixed(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done);
-hipError_t set_smem_limits_fixed(const Geom& g, int mat, size_t bytes);
+hipError_t set_smem_limits_fixed(const Geom& g, size_t bytes);
 
 // Scratch of the allocation-free projection: a file-scope device array of this many bytes per
 // device (noalloc_scratch.hip); its address on the current device.

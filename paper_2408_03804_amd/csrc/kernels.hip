@@ -1,5 +1,5 @@
 // HIP kernels of the Fourier-Galerkin Newton-CG solve for gfx950 (FP64): the pass kernels with
-// the direct FFT stages and their launchers, the reductions, the Newton-level and
+// the direct FFT stages and the launchers, the reductions, the Newton-level and
 // post-processing kernels.  The pass kernels themselves are in pass_kernels.h.
 #include "pass_kernels.h"
 
@@ -330,6 +330,28 @@ __global__ void k_twiddles(double2* tw, int n) {
   }
 }
 
+// Operand fragments of the folded dense DFT of length n from its twiddle table tw[m] = exp(-2 pi i m / n):
+// entry (tile, step, lane) holds (cos, sin)(2 pi k t / n) for output row k = 16 tile + lane mod 16 and
+// folded input t = 1 + 4 step + lane / 16, zero past n / 2, and half of it at t = n / 2, whose folded
+// sum counts the same element twice.
+__global__ void k_dense_frags(const double2* tw, int n, double2* frag) {
+  const int T = n / 2;
+  const int steps = dense_steps(n);
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= dense_rows(n) * steps * 64) return;
+  const int lane = i & 63;
+  const int js = i >> 6;
+  const int k = 16 * (js / steps) + (lane & 15);
+  const int t = 1 + 4 * (js % steps) + (lane >> 4);
+  double2 v = make_double2(0.0, 0.0);
+  if (k <= T && t <= T) {
+    const double2 w = tw[(k * t) % n];
+    const double h = 2 * t == n ? 0.5 : 1.0;
+    v = make_double2(h * w.x, -h * w.y);
+  }
+  frag[i] = v;
+}
+
 // Chirp-z tables of an axis of length n with convolution length m (one block per filter bin k):
 //   chirp[j] = exp(-i pi j^2 / n), j < n;
 //   filt[k] = (1/m) sum_j h_j exp(-2 pi i j k / m), h_j = h_(m-j) = conj(chirp[j]) for j < n, 0 between.
@@ -408,24 +430,25 @@ static inline bool x_fixed128(const Geom& g, const AxisPlan& px, int R, int inpl
 hipError_t launch_xfwd(int prod, int mat, const XFwdArgs& a, int B, hipStream_t s) {
   dim3 grid(nblk_rows(a.g, a.R), B);
   const size_t sm = xfwd_smem(a.g, a.R, a.inplace);
-  if (a.px.m > 0) return launch_xfwd_chirp(prod, mat, a, grid, sm, s);
-  if (a.inplace && a.g.ndim == 3 && fixed_len_kernels(a.px.n)) {
-    bool done = false;
-    const hipError_t e = launch_xfwd_fixed(prod, mat, a, grid, sm, s, &done);
-    if (done) return e;
+  int nf = 0;
+  if (a.px.dense) nf = kDense;
+  else if (a.px.m > 0) nf = kChirp;
+  else if (prod == PROD_CGOP && a.inplace && a.g.ndim == 3 && fixed_len_kernels(a.px.n)) nf = kStaged + a.px.n;
+  else if (prod == PROD_CGOP && x_fixed128(a.g, a.px, a.R, a.inplace)) nf = 128;
+  switch (mat) {
+    case 0: case 1: return xfwd_le(nf, prod, mat, a, grid, sm, s);
+    case 2: case 3: return xfwd_nh(nf, prod, mat, a, grid, sm, s);
+    case 4: case 5: return xfwd_stvk(nf, prod, mat, a, grid, sm, s);
+    case 6: case 7: return xfwd_j2(nf, prod, mat, a, grid, sm, s);
+    case 8: case 9: return xfwd_ps(nf, prod, mat, a, grid, sm, s);
+    default: return hipErrorInvalidValue;
   }
-  if (prod == PROD_CGOP && x_fixed128(a.g, a.px, a.R, a.inplace)) {
-#define FH_C(M, D) hipLaunchKernelGGL((k_xfwd<PROD_CGOP, M, D, (D == 3 ? 128 : 0)>), grid, dim3(kThreads), sm, s, a);
-    FH_DISPATCH_MAT(mat, FH_C)
-#undef FH_C
-    return hipGetLastError();
-  }
-  return dispatch_xfwd<0>(prod, mat, a, grid, sm, s);
 }
 
 hipError_t launch_xinv(int cons, const XInvArgs& a, int B, hipStream_t s) {
   dim3 grid(nblk_rows(a.g, a.R), B);
   const size_t sm = xinv_smem(a.g, a.R, a.inplace);
+  if (a.px.dense) return launch_xinv_dense(cons, a, grid, sm, s);
   if (a.px.m > 0) return launch_xinv_chirp(cons, a, grid, sm, s);
   if (a.inplace && a.g.ndim == 3 && fixed_len_kernels(a.px.n)) {
     bool done = false;
@@ -444,6 +467,7 @@ hipError_t launch_mid(int dir, const AxisArgs& a, int B, hipStream_t s) {
   const bool rows = a.proj && finite_rows(a.g);
   dim3 grid(kx_tiles(a.g.nxh, a.TX), (a.g.nz + a.ZB - 1) / a.ZB, B * (rows ? 3 : a.g.c));
   const size_t sm = mid_smem(a.g, a.TX, a.inplace, a.ZB, a.proj);
+  if (a.pl.dense) return launch_mid_dense(dir, rows, a, grid, sm, s);
   if (a.pl.m > 0) return launch_mid_chirp(dir, rows, a, grid, sm, s);
   if (a.inplace && fixed_len_kernels(a.pl.n)) {
     bool done = false;
@@ -475,6 +499,7 @@ hipError_t launch_outer(int mode, const AxisArgs& a_in, int B, hipStream_t s) {
   dim3 grid(kx_tiles(a.g.nxh, a.TX), a.g.n_mid, B * outer_groups_per_rhs(a.g, mode));
   const size_t sm = outer_smem(a.g, a.TX, a.inplace, mode);
   const bool rows = mode == OUTER_PROJECT && finite_rows(a.g);
+  if (a.pl.dense) return launch_outer_dense(mode, rows, a, grid, sm, s);
   if (a.pl.m > 0) return launch_outer_chirp(mode, rows, a, grid, sm, s);
   if (a.inplace && fixed_len_kernels(a.pl.n)) {
     bool done = false;
@@ -621,6 +646,13 @@ hipError_t launch_plan_tables(AxisPlan* pl, double2* base, hipStream_t s, bool t
     hipLaunchKernelGGL(k_twiddles, dim3((unsigned)((L + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, base, L);
     e = hipGetLastError();
   }
+  if (pl->dense) {
+    const int cnt = (int)dense_elems(pl->n);
+    pl->frag = base + L;
+    hipLaunchKernelGGL(k_dense_frags, dim3((unsigned)((cnt + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, base, pl->n,
+                       base + L);
+    return e == hipSuccess ? hipGetLastError() : e;
+  }
   if (e == hipSuccess && pl->m > 0) {
     hipLaunchKernelGGL(k_chirp_tables, dim3((unsigned)pl->m), dim3(kThreads), 0, s, base + L, base + L + pl->n, pl->n,
                        pl->m);
@@ -651,13 +683,13 @@ hipError_t launch_debug_constitutive(int mat, const double* e, const double* de,
 // Raise the dynamic-LDS limit of the FFT kernels when a plan needs more than 64 KiB.
 hipError_t set_smem_limits(const Geom& g, int mat, size_t bytes) {
   if (bytes <= 65536) return hipSuccess;
-  hipError_t e = pass_smem_limits<0>(g, mat, bytes);
+  hipError_t e = pass_smem_limits<0>(g, bytes);
+  if (e == hipSuccess)
+    e = mat < 2 ? xfwd_le_limits(mat, bytes) : mat < 4 ? xfwd_nh_limits(mat, bytes) : mat < 6 ? xfwd_stvk_limits(mat, bytes)
+        : mat < 8 ? xfwd_j2_limits(mat, bytes) : xfwd_ps_limits(mat, bytes);
   const int attr = (int)hipFuncAttributeMaxDynamicSharedMemorySize;
 #define FH_SET(fn) \
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), (hipFuncAttribute)attr, (int)bytes)
-#define FH_L(M, D) FH_SET((k_xfwd<PROD_CGOP, M, D, (D == 3 ? 128 : 0)>));
-  FH_DISPATCH_MAT(mat, FH_L)
-#undef FH_L
   if (g.c == 6) FH_SET((k_xinv<CONS_CGUPD, 6, 128>));
   if (g.c == 9) FH_SET((k_xinv<CONS_CGUPD, 9, 128>));
   FH_SET((k_mid_frow<-1, 128>));
@@ -665,8 +697,9 @@ hipError_t set_smem_limits(const Geom& g, int mat, size_t bytes) {
   FH_SET((k_outer_frow<128>));
 #undef FH_SET
   if (e == hipSuccess && (g.lx != g.nx || g.lo != g.n_outer || (g.ndim == 3 && g.lm != g.ny)))
-    e = set_smem_limits_chirp(g, mat, bytes);
-  if (e == hipSuccess) e = set_smem_limits_fixed(g, mat, bytes);
+    e = set_smem_limits_chirp(g, bytes);
+  if (e == hipSuccess) e = set_smem_limits_fixed(g, bytes);
+  if (e == hipSuccess && (dense_len(g.nx) || dense_len(g.ny) || dense_len(g.nz))) e = set_smem_limits_dense(g, bytes);
   return e;
 }
 

@@ -5,9 +5,6 @@
 
 namespace fh {
 
-hipError_t launch_xfwd_chirp(int prod, int mat, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s) {
-  return dispatch_xfwd<kChirp>(prod, mat, a, grid, sm, s);
-}
 hipError_t launch_xinv_chirp(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s) {
   return dispatch_xinv<kChirp>(cons, a, grid, sm, s);
 }
@@ -17,6 +14,6 @@ hipError_t launch_mid_chirp(int dir, bool rows, const AxisArgs& a, dim3 grid, si
 hipError_t launch_outer_chirp(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s) {
   return dispatch_outer<kChirp>(mode, rows, a, grid, sm, s);
 }
-hipError_t set_smem_limits_chirp(const Geom& g, int mat, size_t bytes) { return pass_smem_limits<kChirp>(g, mat, bytes); }
+hipError_t set_smem_limits_chirp(const Geom& g, size_t bytes) { return pass_smem_limits<kChirp>(g, bytes); }
 
 }  // namespace fh

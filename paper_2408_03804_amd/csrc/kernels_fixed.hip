@@ -12,19 +12,6 @@ namespace fh {
 namespace {
 
 template <int L>
-hipError_t xfwd_len(int prod, int mat, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done) {
-  *done = prod == PROD_CGOP && (mat == 1 || mat == 3 || mat == 5 || mat == 7);
-  if (!*done) return hipSuccess;
-  switch (mat) {
-    case 1: hipLaunchKernelGGL((k_xfwd<PROD_CGOP, MAT_LE, 3, kStaged + L>), grid, dim3(kThreads), sm, s, a); break;
-    case 3: hipLaunchKernelGGL((k_xfwd<PROD_CGOP, MAT_NH, 3, kStaged + L>), grid, dim3(kThreads), sm, s, a); break;
-    case 5: hipLaunchKernelGGL((k_xfwd<PROD_CGOP, MAT_STVK, 3, kStaged + L>), grid, dim3(kThreads), sm, s, a); break;
-    default: hipLaunchKernelGGL((k_xfwd<PROD_CGOP, MAT_J2, 3, kStaged + L>), grid, dim3(kThreads), sm, s, a); break;
-  }
-  return hipGetLastError();
-}
-
-template <int L>
 hipError_t xinv_len(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done) {
   *done = cons == CONS_CGUPD && (a.g.c == 6 || a.g.c == 9);
   if (!*done) return hipSuccess;
@@ -48,18 +35,11 @@ hipError_t outer_len(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t s
 }
 
 template <int L>
-hipError_t limits_len(int mat, size_t bytes) {
+hipError_t limits_len(size_t bytes) {
   const int attr = (int)hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e = hipSuccess;
 #define FH_SET(fn) \
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), (hipFuncAttribute)attr, (int)bytes)
-  switch (mat) {
-    case 1: FH_SET((k_xfwd<PROD_CGOP, MAT_LE, 3, kStaged + L>)); break;
-    case 3: FH_SET((k_xfwd<PROD_CGOP, MAT_NH, 3, kStaged + L>)); break;
-    case 5: FH_SET((k_xfwd<PROD_CGOP, MAT_STVK, 3, kStaged + L>)); break;
-    case 7: FH_SET((k_xfwd<PROD_CGOP, MAT_J2, 3, kStaged + L>)); break;
-    default: break;
-  }
   FH_SET((k_xinv<CONS_CGUPD, 6, kStaged + L>));
   FH_SET((k_xinv<CONS_CGUPD, 9, kStaged + L>));
   FH_SET((k_mid<-1, kStaged + L>));
@@ -85,13 +65,6 @@ bool fixed_len_kernels(int n) { return n == 96 || n == 64 || n == 48 || n == 32;
     default: break;            \
   }
 
-hipError_t launch_xfwd_fixed(int prod, int mat, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done) {
-  *done = false;
-#define FH_C(L) return xfwd_len<L>(prod, mat, a, grid, sm, s, done);
-  FH_LEN_SWITCH(a.px.n, FH_C)
-#undef FH_C
-  return hipSuccess;
-}
 hipError_t launch_xinv_fixed(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done) {
   *done = false;
 #define FH_C(L) return xinv_len<L>(cons, a, grid, sm, s, done);
@@ -114,11 +87,11 @@ hipError_t launch_outer_fixed(int mode, bool rows, const AxisArgs& a, dim3 grid,
 #undef FH_C
   return hipSuccess;
 }
-hipError_t set_smem_limits_fixed(const Geom& g, int mat, size_t bytes) {
+hipError_t set_smem_limits_fixed(const Geom& g, size_t bytes) {
   hipError_t e = hipSuccess;
   for (int n : {g.nx, g.ny, g.nz}) {
     if (e != hipSuccess || !fixed_len_kernels(n)) continue;
-#define FH_C(L) e = limits_len<L>(mat, bytes); break;
+#define FH_C(L) e = limits_len<L>(bytes); break;
     FH_LEN_SWITCH(n, FH_C)
 #undef FH_C
   }

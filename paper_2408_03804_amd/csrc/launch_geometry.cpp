@@ -65,6 +65,8 @@ bool outer_inplace_ok(const Geom& g, const AxisPlan& pl, int TX, int mode) {
   return inplace_ok(pl, outer_group(g, mode) * kx_tile_max(g.nxh, TX));
 }
 bool inplace_ok(const AxisPlan& pl, int nseq) {
+  if (pl.dense)
+    return dense_rows(pl.n) * ((nseq + kDenseCols - 1) / kDenseCols) <= kDenseHold * (kThreads / 64);
   for (int st = 0; st < pl.nstages; ++st) {
     const int R = pl.radix[st];
     if (R != 2 && R != 3 && R != 4 && R != 5 && R != 8 && R != 16) return false;
@@ -110,7 +112,8 @@ constexpr int kMaxChirpLen = 2048;
 bool make_plan(int n, AxisPlan* pl, int chirp_above) {
   pl->n = n;
   pl->m = 0;
-  pl->tw = pl->chirp = pl->filt = nullptr;
+  pl->tw = pl->chirp = pl->filt = pl->frag = nullptr;
+  pl->dense = 0;
   int rad[kMaxStages], ns = 0;
   const bool ok = factorize(n, rad, &ns);
   int direct = ok ? 0 : 1 << 30;  // sum of the direct stages' prime lengths
@@ -132,7 +135,12 @@ bool make_plan(int n, AxisPlan* pl, int chirp_above) {
   return true;
 }
 
-size_t plan_table_elems(const AxisPlan& pl) { return (size_t)lds_len(pl) + (pl.m > 0 ? (size_t)pl.n + pl.m : 0); }
+bool dense_len(int n) { return n >= 17 && n <= kDenseMax && fixed_nstages(n) == 0; }
+size_t dense_elems(int n) { return (size_t)dense_rows(n) * dense_steps(n) * 64; }
+
+size_t plan_table_elems(const AxisPlan& pl) {
+  return (size_t)lds_len(pl) + (pl.m > 0 ? (size_t)pl.n + pl.m : 0) + (pl.dense ? dense_elems(pl.n) : 0);
+}
 
 void set_lds_lens(Geom* g, const AxisPlan* pl) {
   g->lx = lds_len(pl[0]);

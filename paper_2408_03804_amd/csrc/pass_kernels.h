@@ -79,12 +79,14 @@ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; 
 // The generic kernels hold every compiled schedule, and their registers follow the longest one;
 // the length-specific kernels hold one.  The buffers hold lds_len(pl) rows per sequence.
 constexpr int kChirp = -1;
+constexpr int kDense = -2;  // the folded dense DFT (plans with dense set; kernels_dense.hip)
 constexpr int kStaged = 1 << 12;
 template <int D, int NF>
 __device__ __forceinline__ void pass_fft(double2* A, double2* Bf, int nseq, const AxisPlan& pl, int inplace) {
   if constexpr (NF > kStaged) fixed_stages<NF - kStaged, D, 0, 1>(A, nseq, make_fastdiv((unsigned)nseq), pl.tw);
   else if constexpr (NF > 0) fft_fixed_one<NF, D>(A, nseq, pl.tw);
   else if constexpr (NF == kChirp) fft_chirp<D>(A, Bf, nseq, pl, inplace);
+  else if constexpr (NF == kDense) fft_dense<D>(A, Bf, nseq, pl, inplace);
   else fft_lds_any<D>(A, Bf, nseq, pl, inplace);
 }
 
@@ -396,7 +398,7 @@ __global__ void __launch_bounds__(kThreads) k_xfwd(XFwdArgs a) {
 // ============================================================================
 template <int CONS, int C, int NF = 0>
 // 4 waves per SIMD (at most 128 VGPRs): measured 5 % faster at 128^3 than the unconstrained 166
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) k_xinv(XInvArgs a) {
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NF == kDense ? 3 : 4, 8))) k_xinv(XInvArgs a) {
   const int b = a.active ? a.active[blockIdx.y] : (int)blockIdx.y;
   if (CONS == CONS_CGUPD) {
     if (a.st[b].status != CG_RUNNING) return;
@@ -772,7 +774,7 @@ __global__ void __launch_bounds__(kThreads) k_outer(AxisArgs a) {
 
 template <int DIR, int NF>
 // 4 waves per SIMD (at most 128 VGPRs; 157 unconstrained): measured 15 % faster at 128^3
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) k_mid_frow(AxisArgs a) {
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NF == kDense ? 3 : 4, 8))) k_mid_frow(AxisArgs a) {
   const Geom& g = a.g;
   unsigned bx, by, bz;
   xcd_blocks(&bx, &by, &bz);
@@ -895,7 +897,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4
 // re-indexing), slots (i,0) = v and (i,2) = w of TX bins at one ky.  LDS: element o of sequence
 // (jj, s) at D[o * 2 tw + jj * tw + s].
 template <int NF>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))) k_outer_frow(AxisArgs a) {
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NF == kDense ? 3 : 5, 8))) k_outer_frow(AxisArgs a) {
   const Geom& g = a.g;
   unsigned bx, by, bz;
   xcd_blocks(&bx, &by, &bz);
@@ -964,24 +966,6 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5
 // launches of the pass kernels with FFT variant NF (grid and LDS bytes from the caller)
 // ============================================================================
 template <int NF>
-hipError_t dispatch_xfwd(int prod, int mat, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s) {
-#define FH_L(M, D)                                                                                             \
-  switch (prod) {                                                                                              \
-    case PROD_IDENT: hipLaunchKernelGGL((k_xfwd<PROD_IDENT, M, D, NF>), grid, dim3(kThreads), sm, s, a); break;   \
-    case PROD_STRESS: hipLaunchKernelGGL((k_xfwd<PROD_STRESS, M, D, NF>), grid, dim3(kThreads), sm, s, a); break; \
-    case PROD_CGOP: hipLaunchKernelGGL((k_xfwd<PROD_CGOP, M, D, NF>), grid, dim3(kThreads), sm, s, a); break;     \
-    case PROD_TRHS: hipLaunchKernelGGL((k_xfwd<PROD_TRHS, M, D, NF>), grid, dim3(kThreads), sm, s, a); break;     \
-    case PROD_CGOP_STORED:                                                                                     \
-      hipLaunchKernelGGL((k_xfwd<PROD_CGOP_STORED, M, D, NF>), grid, dim3(kThreads), sm, s, a); break;         \
-    case PROD_ADJ: hipLaunchKernelGGL((k_xfwd<PROD_ADJ, M, D, NF>), grid, dim3(kThreads), sm, s, a); break;       \
-    default: return hipErrorInvalidValue;                                                                      \
-  }
-  FH_DISPATCH_MAT(mat, FH_L)
-#undef FH_L
-  return hipGetLastError();
-}
-
-template <int NF>
 hipError_t dispatch_xinv(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s) {
 #define FH_L(CC)                                                                                              \
   switch (cons) {                                                                                             \
@@ -1037,22 +1021,14 @@ hipError_t dispatch_outer(int mode, bool rows, const AxisArgs& a, dim3 grid, siz
   return hipGetLastError();
 }
 
-// Dynamic-LDS limit of every pass kernel of variant NF that a grid of this kind launches.
+// Dynamic-LDS limit of every pass kernel of variant NF that a grid of this kind launches (the
+// forward x pass: xfwd_limits).
 template <int NF>
-hipError_t pass_smem_limits(const Geom& g, int mat, size_t bytes) {
+hipError_t pass_smem_limits(const Geom& g, size_t bytes) {
   const int attr = (int)hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e = hipSuccess;
 #define FH_SET(fn) \
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), (hipFuncAttribute)attr, (int)bytes)
-#define FH_L(M, D)                          \
-  FH_SET((k_xfwd<PROD_IDENT, M, D, NF>));   \
-  FH_SET((k_xfwd<PROD_STRESS, M, D, NF>));  \
-  FH_SET((k_xfwd<PROD_CGOP, M, D, NF>));    \
-  FH_SET((k_xfwd<PROD_TRHS, M, D, NF>));    \
-  FH_SET((k_xfwd<PROD_CGOP_STORED, M, D, NF>)); \
-  FH_SET((k_xfwd<PROD_ADJ, M, D, NF>));
-  FH_DISPATCH_MAT(mat, FH_L)
-#undef FH_L
 #define FH_X(CC) FH_SET((k_xinv<CONS_IDENT, CC, NF>)); FH_SET((k_xinv<CONS_RHS, CC, NF>)); FH_SET((k_xinv<CONS_CGUPD, CC, NF>));
   switch (g.c) {
     case 3: FH_X(3); break;
