@@ -11,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfft_homog.so")
-CG_SOURCES = ["kernels.hip", "kernels_chirp.hip", "kernels_dense.hip", "kernels_fixed.hip", "xpass_le.hip", "xpass_nh.hip",
+CG_SOURCES = ["kernels.hip", "kernels_radix.hip", "kernels_radix_outer.hip", "kernels_radix_cg.hip", "kernels_chirp.hip",
+              "kernels_dense.hip", "kernels_fixed.hip", "xpass_le.hip", "xpass_nh.hip",
               "xpass_stvk.hip", "xpass_j2.hip", "xpass_ps.hip"]
 SOURCES = CG_SOURCES + ["fft_homog.hip", "cnn.hip", "launch_geometry.cpp", "noalloc_scratch.hip"]
 HEADERS = ["common.h", "dual.h", "materials.h", "fft_lds.h", "kernels.h", "pass_kernels.h", "xpass_law.h"]

@@ -25,6 +25,8 @@ constexpr size_t kAlign = 256;
 constexpr int kResults = 128;
 constexpr int kChunk = 8;          // CG iterations enqueued between host checks
 constexpr int kTimedLaunches = 7;  // launches of one CG iteration (kernel timing)
+// slot of fft_homog_debug_time_cg's ms of each launch of the CG on displacements, in launch order
+constexpr int kDispSlot[kTimedLaunches] = {5, 4, 0, 1, 2, 3, 6};
 constexpr size_t kLdsFft = 48 * 1024;
 constexpr size_t kLdsOuter = 64 * 1024;
 constexpr size_t kLdsMax = 160 * 1024;
@@ -40,8 +42,8 @@ constexpr size_t kStaggers[] = {0, 256, 16u << 10, 256u << 10, 2u << 20, 4u << 2
 int ncomp_of(int kin, int ndim) { return kin == FFT_HOMOG_SMALL_STRAIN ? (ndim == 3 ? 6 : 3) : ndim * ndim; }
 
 struct Layout {
-  size_t F, x, r, p, spec, kst, phase, density, scale, table, hist, tw[3], partials, state, active, results, flags,
-      total;
+  size_t F, x, r, p, spec, kst, phase, density, scale, table, hist, tw[3], partials, rr_partials, state, active, results,
+      flags, total;
   size_t slack;  // bytes behind the spectrum that the work vectors may be staggered into
   int cells;  // independent cells (microstructures) of this grid held by the handle
   int B, R, TXm, TXo, nblk_x, nblk_vox;
@@ -240,9 +242,11 @@ int make_layout_with(const fft_homog_desc* d, Layout* L, int plans) {
   };
   const size_t fld = (size_t)C * g.N * sizeof(double);
   L->F = take(fld);
-  L->x = take(fld * L->B);
-  L->r = take(fld * L->B);
-  L->p = take(fld * L->B);
+  // x, r, p: strain fields, or the CG on displacements' half spectra [d][Nh]
+  const size_t vec = std::max<size_t>(fld, (size_t)d->ndim * g.Nh * sizeof(double2)) * L->B;
+  L->x = take(vec);
+  L->r = take(vec);
+  L->p = take(vec);
   L->spec = take((size_t)L->B * C * g.Nh * sizeof(double2));
   // On large grids the work vectors get room to be staggered (fft_homog_tune_placement): F, x, r
   // and p sit at multiples of the component size from one another, and their relative placement
@@ -263,6 +267,8 @@ int make_layout_with(const fft_homog_desc* d, Layout* L, int plans) {
   np = std::max(np, (size_t)(C + 1) * L->nblk_vox);
   L->n_partials = np;
   L->partials = take(np * sizeof(double));
+  // <r, r> of the CG on displacements: one partial per outer-pass block, one bin wide at the least
+  L->rr_partials = take((size_t)L->B * g.nxh * g.n_mid * outer_groups_per_rhs(g) * sizeof(double));
   L->state = take((size_t)L->B * sizeof(CgState));
   L->active = take((size_t)L->B * sizeof(int));
   L->n_results = std::max((size_t)kResults, (size_t)L->cells * C * C);
@@ -341,7 +347,7 @@ struct fft_homog {
   int matcode;
   hipStream_t stream;
   char* ws;
-  double *F, *x, *r, *p, *kst, *partials, *results, *table, *density, *scale, *hist;
+  double *F, *x, *r, *p, *kst, *partials, *rr_partials, *results, *table, *density, *scale, *hist;
   bool j2_pending;  // J2: the last converged load step is not yet committed to the history
   double simp_p;
   double2* spec;
@@ -354,6 +360,7 @@ struct fft_homog {
   MatParams mat;
   double macro_cur[kMaxC];
   bool solved_ok;
+  bool disp;  // CG on displacements (else on strain fields)
   // pinned host mirror of the device records
   CgState* h_st;
   double* h_results;
@@ -408,6 +415,7 @@ XFwdArgs xfwd_args(fft_homog_t* h) {
   a.R = h->L.R;
   a.nblocks = h->L.nblk_x;
   a.inplace = h->L.in_x;
+  a.scale = 1.0 / (double)h->g.N;
   a.x = h->x;
   a.F = h->F;
   a.Kst = h->kst;
@@ -439,6 +447,7 @@ XInvArgs xinv_args(fft_homog_t* h) {
 // proj: the pass belongs to a projection chain (y pass: the row-wise finite-strain kernels)
 AxisArgs axis_args(fft_homog_t* h, int axis, int TX, const CgState* st, int inplace = -1, int proj = 1) {
   AxisArgs a;
+  memset(&a, 0, sizeof(a));
   a.g = h->g;
   a.pl = h->plan[axis];
   a.TX = TX;
@@ -447,10 +456,34 @@ AxisArgs axis_args(fft_homog_t* h, int axis, int TX, const CgState* st, int inpl
   a.ZB = (axis == 1 && h->g.ndim == 3) ? mid_planes(h->g, h->plan[1], TX, a.inplace, h->L.B, proj) : 1;
   a.spec = h->spec;
   a.st = st;
-  a.active = nullptr;
-  a.pq_st = nullptr;
-  a.pq_partials = nullptr;
-  a.pq_nblocks = 0;
+  return a;
+}
+
+// CG on displacements (3D): the outer pass for a tile of TX bins, the forward y pass (alpha: it sums <p, K:p>)
+AxisArgs cg_outer_args(fft_homog_t* h, int TX, int inplace = -1) {
+  AxisArgs a = axis_args(h, h->g.ndim - 1, TX, h->st, inplace);
+  a.xu = (double2*)h->x;
+  a.ru = (double2*)h->r;
+  a.pu = (double2*)h->p;
+  a.rr_partials = h->rr_partials;
+  a.rr_nblocks = kx_tiles(h->g.nxh, TX) * h->g.n_mid * outer_groups_per_rhs(h->g);
+  a.inv_n = 1.0 / (double)h->g.N;
+  // x, r and p pass the caches by where they and the spectrum do not fit the 256 MB Infinity Cache
+  // together, so that the y passes find the spectrum there (128^3, y^-1: 64 -> 50 us), and a tile's rows
+  // are whole lines (part lines written past the caches cost more than they save: at 64^3, where all
+  // fits, and 4 bins the inverse pass took 39 us with it).
+  const double bytes = (3.0 * h->desc.ndim + h->g.c) * h->g.Nh * sizeof(double2) * h->L.B;
+  a.stream = bytes > 256e6 && TX % 8 == 0 && h->g.nxp % 8 == 0;
+  return a;
+}
+AxisArgs cg_mid_args(fft_homog_t* h, const CgState* st, bool alpha) {
+  AxisArgs a = axis_args(h, 1, h->L.TXm, st);
+  a.mirror = 1;
+  if (alpha) {
+    a.pq_st = h->st;
+    a.pq_partials = h->partials;
+    a.pq_nblocks = h->L.nblk_x;
+  }
   return a;
 }
 
@@ -469,6 +502,41 @@ hipError_t enqueue_spectral(fft_homog_t* h, int mode, int B, const CgState* st, 
 
 int spectral_middle(fft_homog_t* h, int mode, int B, const CgState* st) {
   FH_CK(enqueue_spectral(h, mode, B, st, h->stream));
+  return FFT_HOMOG_OK;
+}
+
+// The source's spectrum (in h->spec after the x pass) becomes the right-hand side b = -G*(source):
+// r = b, <b, b>, CG records (and x = 0 where the CG runs on strain fields).
+int enqueue_rhs(fft_homog_t* h, int B) {
+  FH_CK(launch_cg_reduce(RED_SRC, h->st, h->partials, h->L.nblk_x, B, h->stream));
+  if (h->disp) {
+    const AxisArgs ao = cg_outer_args(h, h->L.TXo);
+    FH_CK(launch_mid(-1, cg_mid_args(h, nullptr, false), B, h->stream));
+    FH_CK(launch_outer(OUTER_RHS, ao, B, h->stream));
+    FH_CK(launch_cg_reduce(RED_RHS, h->st, h->rr_partials, ao.rr_nblocks, B, h->stream));
+    return FFT_HOMOG_OK;
+  }
+  FH_CK(enqueue_spectral(h, OUTER_PROJECT, B, nullptr, h->stream));
+  FH_CK(launch_xinv(CONS_RHS, xinv_args(h), B, h->stream));
+  FH_CK(launch_cg_reduce(RED_RHS, h->st, h->partials, h->L.nblk_x, B, h->stream));
+  return FFT_HOMOG_OK;
+}
+
+// CG on displacements: strain fields of the solution (OUTER_SOLUTION; its displacement is overwritten if
+// out == h->x) or of the residual (OUTER_RESIDUAL) of B right-hand sides.
+int expand_strain(fft_homog_t* h, int mode, int B, double* out) {
+  FH_CK(launch_outer(mode, cg_outer_args(h, h->L.TXo), B, h->stream));
+  FH_CK(launch_mid(1, axis_args(h, 1, h->L.TXm, nullptr), B, h->stream));
+  XInvArgs ai = xinv_args(h);
+  ai.out = out;
+  FH_CK(launch_xinv(CONS_IDENT, ai, B, h->stream));
+  return FFT_HOMOG_OK;
+}
+
+// The last CG update of x, and x as strain fields in h->x.
+int finish_solution(fft_homog_t* h, int B) {
+  if (h->disp) return expand_strain(h, OUTER_SOLUTION, B, h->x);
+  FH_CK(launch_cg_finish(h->x, h->p, h->st, h->g, B, h->stream));
   return FFT_HOMOG_OK;
 }
 
@@ -494,7 +562,7 @@ int harvest_timing(fft_homog_t* h) {
     for (int k = 0; k < kTimedLaunches; ++k) {
       float t = 0.f;
       FH_CK(hipEventElapsedTime(&t, ev[k], ev[k + 1]));
-      h->time_acc[k] += t;
+      h->time_acc[h->disp ? kDispSlot[k] : k] += t;
     }
     ++h->time_samples;
   }
@@ -511,49 +579,71 @@ void place_work_vectors(fft_homog_t* h, size_t s) {
   h->stagger = s;
 }
 
+// The launches of one CG iteration, in order.  Slot 3 (CG on displacements) or 1 (on strain fields) is
+// where a separate <p, K:p> reduction would sit: it is done inside the launch after it.
+struct CgLaunches {
+  fft_homog_t* h;
+  bool disp, three, stored;
+  XFwdArgs x;
+  XInvArgs xi;
+  AxisArgs mf, mi, o;
+  const int* active;
+  CgLaunches(fft_homog_t* h_, const int* active_)
+      : h(h_), disp(h_->disp), three(h_->g.ndim == 3), stored(h_->desc.k_mode == FFT_HOMOG_K_STORED), x(xfwd_args(h_)),
+        xi(xinv_args(h_)), active(active_) {
+    mi = axis_args(h, 1, h->L.TXm, h->st);
+    if (disp) {
+      mf = cg_mid_args(h, h->st, true);
+      o = cg_outer_args(h, h->L.TXo);
+    } else {
+      mf = mi;
+      o = axis_args(h, h->g.ndim - 1, h->L.TXo, h->st);
+      o.pq_st = h->st;
+      o.pq_partials = h->partials;
+      o.pq_nblocks = h->L.nblk_x;
+      x.in = h->r;
+      x.p = h->p;
+    }
+    x.active = xi.active = mf.active = mi.active = o.active = active;
+  }
+  // slot of fft_homog_debug_time_cg's ms
+  int slot(int k) const {
+    return disp ? kDispSlot[k] : k;
+  }
+  hipError_t launch(int k, int B, hipStream_t s) const {
+    switch (slot(k)) {
+      case 0:
+        if (disp) return launch_xfwd(stored ? PROD_XOP_STORED : PROD_XOP, h->matcode, x, B, s);
+        return launch_xfwd(stored ? PROD_CGOP_STORED : PROD_CGOP, h->matcode, x, B, s);
+      case 1: return hipSuccess;
+      case 2: return three ? launch_mid(-1, mf, B, s) : hipSuccess;
+      case 3: return launch_outer(disp ? OUTER_CGFWD : OUTER_PROJECT, o, B, s);
+      case 4: return three ? launch_mid(1, mi, B, s) : hipSuccess;
+      case 5: return disp ? launch_outer(OUTER_CGINV, o, B, s) : launch_xinv(CONS_CGUPD, xi, B, s);
+      default:
+        return disp ? launch_cg_reduce(RED_RR, h->st, h->rr_partials, o.rr_nblocks, B, s, active)
+                    : launch_cg_reduce(RED_RR, h->st, h->partials, h->L.nblk_x, B, s, active);
+    }
+  }
+};
+
 // m CG iterations, enqueued on stream s, over B launch slots: slot i is right-hand side
 // active[i] (active == nullptr: i).  Right-hand sides that stop inside the chunk make
 // their blocks return at once.  With kernel timing on (and s the handle's own stream, not a
 // graph capture), every time_every-th iteration gets an event before its first launch and
 // after each launch.
 hipError_t enqueue_cg_iters(fft_homog_t* h, int B, int m, hipStream_t s, const int* active = nullptr) {
-  const int prod = h->desc.k_mode == FFT_HOMOG_K_STORED ? PROD_CGOP_STORED : PROD_CGOP;
-  XFwdArgs a = xfwd_args(h);
-  a.in = h->r;
-  a.p = h->p;
-  a.active = active;
-  XInvArgs ai = xinv_args(h);
-  ai.active = active;
-  AxisArgs am = axis_args(h, 1, h->L.TXm, h->st);
-  AxisArgs ao = axis_args(h, h->g.ndim - 1, h->L.TXo, h->st);
-  am.active = ao.active = active;
-  ao.pq_st = h->st;
-  ao.pq_partials = h->partials;
-  ao.pq_nblocks = h->L.nblk_x;
-  const bool three = h->g.ndim == 3;
+  const CgLaunches L(h, active);
   const bool timing = h->time_every > 0 && s == h->stream;
   hipError_t e = hipSuccess;
   for (int i = 0; i < m && e == hipSuccess; ++i) {
     hipEvent_t* ev = nullptr;
     if (timing && h->time_count++ % h->time_every == 0) e = timing_events(h, &ev);
-    int k = 0;
-    auto mark = [&]() {
-      if (ev && e == hipSuccess) e = hipEventRecord(ev[k++], s);
-    };
-    mark();
-    if (e == hipSuccess) e = launch_xfwd(prod, h->matcode, a, B, s);
-    mark();
-    mark();  // <p, K:p> is reduced inside the outer pass
-    if (e == hipSuccess && three) e = launch_mid(-1, am, B, s);
-    mark();
-    if (e == hipSuccess) e = launch_outer(OUTER_PROJECT, ao, B, s);
-    mark();
-    if (e == hipSuccess && three) e = launch_mid(1, am, B, s);
-    mark();
-    if (e == hipSuccess) e = launch_xinv(CONS_CGUPD, ai, B, s);
-    mark();
-    if (e == hipSuccess) e = launch_cg_reduce(RED_RR, h->st, h->partials, h->L.nblk_x, B, s, active);
-    mark();
+    if (ev && e == hipSuccess) e = hipEventRecord(ev[0], s);
+    for (int k = 0; k < kTimedLaunches && e == hipSuccess; ++k) {
+      e = L.launch(k, B, s);
+      if (ev && e == hipSuccess) e = hipEventRecord(ev[k + 1], s);
+    }
   }
   return e;
 }
@@ -621,11 +711,8 @@ int rhs_chain(fft_homog_t* h, int prod, int B, const double* unit) {
   if (unit)
     for (int k = 0; k < h->g.c; ++k) a.unit[k] = unit[k];
   FH_CK(launch_xfwd(prod, h->matcode, a, B, h->stream));
-  FH_CK(launch_cg_reduce(RED_SRC, h->st, h->partials, h->L.nblk_x, B, h->stream));
-  rc = spectral_middle(h, OUTER_PROJECT, B, nullptr);
+  rc = enqueue_rhs(h, B);
   if (rc) return rc;
-  FH_CK(launch_xinv(CONS_RHS, xinv_args(h), B, h->stream));
-  FH_CK(launch_cg_reduce(RED_RHS, h->st, h->partials, h->L.nblk_x, B, h->stream));
   return read_states(h, B);
 }
 
@@ -652,7 +739,8 @@ int cg_chunk_length(int iters, double rr0, double rr, double tol, int prev_iters
   return m;
 }
 
-// Conjugate gradients on all running right-hand sides until none is running.  Once some
+// Conjugate gradients on all running right-hand sides until none is running; the solutions as strain
+// fields in h->x.  Once some
 // have stopped, the launches cover only the running ones (their indices are uploaded
 // before each chunk), so a batch's slow tail does not pay for its finished members.
 int cg_loop(fft_homog_t* h, int B) {
@@ -667,7 +755,7 @@ int cg_loop(fft_homog_t* h, int B) {
         h->h_active[nrun++] = b;
         done = std::min(done, h->h_st[b].iters);
       }
-    if (nrun == 0) return FFT_HOMOG_OK;
+    if (nrun == 0) return finish_solution(h, B);
     // Iterations to enqueue before the next host check.  A single right-hand side (not replayed
     // from a graph) takes up to 2 kChunk at once while far from the tolerance and about the
     // predicted remainder near it, from its mean residual decay per iteration so far: fewer
@@ -694,12 +782,6 @@ int cg_loop(fft_homog_t* h, int B) {
     if (h->tev_used) {
       rc = harvest_timing(h);
       if (rc) return rc;
-    }
-    bool still = false;
-    for (int b = 0; b < B; ++b) still = still || h->h_st[b].status == CG_RUNNING;
-    if (!still) {
-      FH_CK(launch_cg_finish(h->x, h->p, h->st, h->g, B, h->stream));
-      return FFT_HOMOG_OK;
     }
   }
 }
@@ -823,6 +905,8 @@ int fft_homog_create(const fft_homog_desc* d, void* dev_workspace, size_t bytes,
   h->scale = (d->flags & FFT_HOMOG_FLAG_DENSITY) ? (double*)(h->ws + L.scale) : nullptr;
   h->table = (double*)(h->ws + L.table);
   h->partials = (double*)(h->ws + L.partials);
+  h->rr_partials = (double*)(h->ws + L.rr_partials);
+  h->disp = d->ndim == 3 && d->tol_cg >= kDisplacementTol;
   h->st = (CgState*)(h->ws + L.state);
   h->results = (double*)(h->ws + L.results);
   h->flags = (int*)(h->ws + L.flags);
@@ -1151,11 +1235,8 @@ int fft_homog_adjoint(fft_homog_t* h, const double* w_stress, double w_energy, d
   int rc = upload_states(h, 1);
   if (rc) return rc;
   FH_CK(launch_xfwd(PROD_ADJ, h->matcode, a, 1, h->stream));
-  FH_CK(launch_cg_reduce(RED_SRC, h->st, h->partials, h->L.nblk_x, 1, h->stream));
-  rc = spectral_middle(h, OUTER_PROJECT, 1, nullptr);
+  rc = enqueue_rhs(h, 1);
   if (rc) return rc;
-  FH_CK(launch_xinv(CONS_RHS, xinv_args(h), 1, h->stream));
-  FH_CK(launch_cg_reduce(RED_RHS, h->st, h->partials, h->L.nblk_x, 1, h->stream));
   rc = read_states(h, 1);
   if (rc) return rc;
   if (h->kst) FH_CK(launch_store_tangent(h->matcode, h->F, h->mat, h->kst, h->g, h->stream));
@@ -1340,14 +1421,17 @@ int fft_homog_debug_cg(fft_homog_t* h, int iters, double* x_out, double* r_out) 
   FH_CK(hipMemcpyAsync(h->st, h->h_st, sizeof(CgState), hipMemcpyHostToDevice, h->stream));
   if (h->kst) FH_CK(launch_store_tangent(h->matcode, h->F, h->mat, h->kst, h->g, h->stream));
   FH_CK(enqueue_cg_iters(h, 1, iters, h->stream));
-  FH_CK(launch_cg_finish(h->x, h->p, h->st, h->g, 1, h->stream));
+  rc = finish_solution(h, 1);
+  if (rc) return rc;
   rc = read_states(h, 1);
   if (rc) return rc;
   if (h->h_st[0].status != CG_MAXIT || h->h_st[0].iters != iters)
     return fail(h, FFT_HOMOG_EBREAKDOWN, "CG stopped before the requested iteration count");
   const size_t bytes = (size_t)h->g.c * h->g.N * sizeof(double);
   FH_CK(hipMemcpyAsync(x_out, h->x, bytes, hipMemcpyDeviceToDevice, h->stream));
-  FH_CK(hipMemcpyAsync(r_out, h->r, bytes, hipMemcpyDeviceToDevice, h->stream));
+  if (h->disp) rc = expand_strain(h, OUTER_RESIDUAL, 1, r_out);
+  else FH_CK(hipMemcpyAsync(r_out, h->r, bytes, hipMemcpyDeviceToDevice, h->stream));
+  if (rc) return rc;
   FH_CK(hipStreamSynchronize(h->stream));
   return FFT_HOMOG_OK;
 }
@@ -1369,41 +1453,22 @@ int fft_homog_debug_time_cg(fft_homog_t* h, int iters, double* ms) {
   h->h_st[0].max_iters = iters + 1;
   FH_CK(hipMemcpyAsync(h->st, h->h_st, sizeof(CgState), hipMemcpyHostToDevice, h->stream));
   if (h->kst) FH_CK(launch_store_tangent(h->matcode, h->F, h->mat, h->kst, h->g, h->stream));
-  const int prod = h->kst ? PROD_CGOP_STORED : PROD_CGOP;
-  XFwdArgs a = xfwd_args(h);
-  a.in = h->r;
-  a.p = h->p;
-  XInvArgs ai = xinv_args(h);
-  AxisArgs ao = axis_args(h, h->g.ndim - 1, h->L.TXo, h->st);
-  ao.pq_st = h->st;
-  ao.pq_partials = h->partials;
-  ao.pq_nblocks = h->L.nblk_x;
-  const bool three = h->g.ndim == 3;
+  const CgLaunches L(h, nullptr);
   hipEvent_t ev[8];
   for (int k = 0; k < 8; ++k) FH_CK(hipEventCreate(&ev[k]));
   double acc[7] = {0, 0, 0, 0, 0, 0, 0};
   int status = FFT_HOMOG_OK;
   for (int i = 0; i < iters && status == FFT_HOMOG_OK; ++i) {
     hipError_t e = hipEventRecord(ev[0], h->stream);
-    if (e == hipSuccess) e = launch_xfwd(prod, h->matcode, a, 1, h->stream);
-    if (e == hipSuccess) e = hipEventRecord(ev[1], h->stream);
-    // <p, K:p> is reduced inside the outer pass: its slot stays empty
-    if (e == hipSuccess) e = hipEventRecord(ev[2], h->stream);
-    if (e == hipSuccess && three) e = launch_mid(-1, axis_args(h, 1, h->L.TXm, h->st), 1, h->stream);
-    if (e == hipSuccess) e = hipEventRecord(ev[3], h->stream);
-    if (e == hipSuccess) e = launch_outer(OUTER_PROJECT, ao, 1, h->stream);
-    if (e == hipSuccess) e = hipEventRecord(ev[4], h->stream);
-    if (e == hipSuccess && three) e = launch_mid(1, axis_args(h, 1, h->L.TXm, h->st), 1, h->stream);
-    if (e == hipSuccess) e = hipEventRecord(ev[5], h->stream);
-    if (e == hipSuccess) e = launch_xinv(CONS_CGUPD, ai, 1, h->stream);
-    if (e == hipSuccess) e = hipEventRecord(ev[6], h->stream);
-    if (e == hipSuccess) e = launch_cg_reduce(RED_RR, h->st, h->partials, h->L.nblk_x, 1, h->stream);
-    if (e == hipSuccess) e = hipEventRecord(ev[7], h->stream);
+    for (int k = 0; k < kTimedLaunches && e == hipSuccess; ++k) {
+      e = L.launch(k, 1, h->stream);
+      if (e == hipSuccess) e = hipEventRecord(ev[k + 1], h->stream);
+    }
     if (e == hipSuccess) e = hipEventSynchronize(ev[7]);
     for (int k = 0; k < 7 && e == hipSuccess; ++k) {
       float t = 0.f;
       e = hipEventElapsedTime(&t, ev[k], ev[k + 1]);
-      acc[k] += t;
+      acc[L.slot(k)] += t;
     }
     if (e != hipSuccess) status = fail(h, FFT_HOMOG_EDEVICE, hipGetErrorString(e));
   }
@@ -1475,10 +1540,11 @@ int fft_homog_autotune(fft_homog_t* h, int reps, int* shape) {
   FH_CK(hipMemsetAsync(h->x, 0, vec, h->stream));
   FH_CK(hipMemsetAsync(h->r, 0, vec, h->stream));
   FH_CK(hipMemsetAsync(h->p, 0, vec, h->stream));
+  FH_CK(hipMemsetAsync(h->spec, 0, (size_t)Bt * C * g.Nh * sizeof(double2), h->stream));
   int rc = upload_states(h, Bt);
   if (rc) return rc;
   if (h->kst) FH_CK(launch_store_tangent(h->matcode, h->F, h->mat, h->kst, g, h->stream));
-  const int prod = h->kst ? PROD_CGOP_STORED : PROD_CGOP;
+  const int prod = h->disp ? (h->kst ? PROD_XOP_STORED : PROD_XOP) : h->kst ? PROD_CGOP_STORED : PROD_CGOP;
 
   // The spectrum row pitch is tuned with the rest: the default pads rows to 8 bins (whole
   // 128-byte lines for the y and outer tiles); unpadded rows move fewer bytes, which pays on
@@ -1519,7 +1585,7 @@ int fft_homog_autotune(fft_homog_t* h, int reps, int* shape) {
             double ms = 0.0;
             FH_CK(time_launches(h, reps, [&]() {
               hipError_t e = launch_xfwd(prod, h->matcode, a, Bt, h->stream);
-              return e == hipSuccess ? launch_xinv(CONS_CGUPD, ai, Bt, h->stream) : e;
+              return e == hipSuccess && !h->disp ? launch_xinv(CONS_CGUPD, ai, Bt, h->stream) : e;
             }, &ms));
             if (incumbent) bt = ms;
             else if (ms < kGain * bt) { bt = ms; cur.R = r; cur.in_x = ip; }
@@ -1557,9 +1623,13 @@ int fft_homog_autotune(fft_homog_t* h, int reps, int* shape) {
             if ((pass == 0) != incumbent) continue;
             if (ip && !outer_inplace_ok(g, pouter, t)) continue;
             if (!incumbent && outer_smem(g, t, ip) > kLdsTune) continue;
-            const AxisArgs a = axis_args(h, g.ndim - 1, t, h->st, ip);
+            const AxisArgs a = h->disp ? cg_outer_args(h, t, ip) : axis_args(h, g.ndim - 1, t, h->st, ip);
             double ms = 0.0;
-            FH_CK(time_launches(h, reps, [&]() { return launch_outer(OUTER_PROJECT, a, Bt, h->stream); }, &ms));
+            FH_CK(time_launches(h, reps, [&]() {
+              if (!h->disp) return launch_outer(OUTER_PROJECT, a, Bt, h->stream);
+              hipError_t e = launch_outer(OUTER_CGINV, a, Bt, h->stream);
+              return e == hipSuccess ? launch_outer(OUTER_CGFWD, a, Bt, h->stream) : e;
+            }, &ms));
             if (incumbent) bt = ms;
             else if (ms < kGain * bt) { bt = ms; cur.TXo = t; cur.in_o = ip; }
           }
@@ -1605,7 +1675,7 @@ int fft_homog_tune_placement(fft_homog_t* h, int reps, size_t* stagger) {
   const int Bt = (int)std::max(1LL, std::min((long long)B, (1LL << 22) / g.N));
   const double kGain = 0.98;  // a new placement must be clearly faster than the incumbent
   drop_graphs(h);
-  const int prod = h->kst ? PROD_CGOP_STORED : PROD_CGOP;
+  const int prod = h->disp ? (h->kst ? PROD_XOP_STORED : PROD_XOP) : h->kst ? PROD_CGOP_STORED : PROD_CGOP;
   const size_t vec = (size_t)Bt * g.c * g.N * sizeof(double);
   const size_t inc = h->stagger;
   size_t best = inc;
@@ -1622,14 +1692,18 @@ int fft_homog_tune_placement(fft_homog_t* h, int reps, size_t* stagger) {
       FH_CK(hipMemsetAsync(h->p, 0, vec, h->stream));
       const int rc = upload_states(h, Bt);
       if (rc) return rc;
+      FH_CK(hipMemsetAsync(h->spec, 0, (size_t)Bt * g.c * g.Nh * sizeof(double2), h->stream));
       XFwdArgs a = xfwd_args(h);
       a.in = h->r;
       a.p = h->p;
       XInvArgs ai = xinv_args(h);
+      const AxisArgs ao = cg_outer_args(h, h->L.TXo);
       double ms = 0.0;
       FH_CK(time_launches(h, reps, [&]() {
         hipError_t e = launch_xfwd(prod, h->matcode, a, Bt, h->stream);
-        return e == hipSuccess ? launch_xinv(CONS_CGUPD, ai, Bt, h->stream) : e;
+        if (!h->disp) return e == hipSuccess ? launch_xinv(CONS_CGUPD, ai, Bt, h->stream) : e;
+        if (e == hipSuccess) e = launch_outer(OUTER_CGFWD, ao, Bt, h->stream);
+        return e == hipSuccess ? launch_outer(OUTER_CGINV, ao, Bt, h->stream) : e;
       }, &ms));
       if (incumbent) best_t = ms;
       else if (ms < kGain * best_t) {

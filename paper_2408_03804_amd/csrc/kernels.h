@@ -5,9 +5,23 @@
 
 namespace fh {
 
-enum Producer { PROD_IDENT = 0, PROD_STRESS = 1, PROD_CGOP = 2, PROD_TRHS = 3, PROD_CGOP_STORED = 4, PROD_ADJ = 5 };
+// PROD_CGOP*: the forward x pass of the CG on strain fields; PROD_XOP*: the x pass of the CG on displacements
+enum Producer {
+  PROD_IDENT = 0, PROD_STRESS = 1, PROD_CGOP = 2, PROD_TRHS = 3, PROD_CGOP_STORED = 4, PROD_ADJ = 5,
+  PROD_XOP = 6, PROD_XOP_STORED = 7
+};
 enum Consumer { CONS_IDENT = 0, CONS_RHS = 1, CONS_CGUPD = 2 };
-enum OuterMode { OUTER_PROJECT = 0, OUTER_FWD = 1, OUTER_INV = 2 };
+// projection and plain transforms; CG on displacements: the iteration's forward and inverse passes,
+// the right-hand side, the expansion of the solution or of the residual
+enum OuterMode {
+  OUTER_PROJECT = 0, OUTER_FWD = 1, OUTER_INV = 2, OUTER_CGFWD = 3, OUTER_RHS = 4, OUTER_CGINV = 5,
+  OUTER_SOLUTION = 6, OUTER_RESIDUAL = 7
+};
+inline bool outer_cg_mode(int mode) { return mode >= OUTER_CGFWD; }
+// 3D grids with a CG tolerance from here on run the CG on displacements (pass_kernels.h).  A 2D grid has
+// no y pass to save the traffic in, its launches are what an iteration costs: 25.2 ms on strain fields
+// against 27.2 on displacements per solve at 299^2.
+constexpr double kDisplacementTol = 1e-11;
 enum Reduce { RED_SRC = 0, RED_RHS = 1, RED_PQ = 2, RED_RR = 3 };
 
 // x-axis forward pass: per-voxel producer, then real-to-complex FFT along x.
@@ -30,6 +44,7 @@ struct XFwdArgs {
   double* partials;      // [B][nblocks]
   double unit[kMaxC];    // TRHS: load l of a cell is unit[l] * e_l in the packed basis; ADJ: packed W
   double w_energy;       // ADJ: weight of the energy in the objective
+  double scale;          // XOP: 1 / N of the inverse transform
 };
 
 // x-axis inverse pass: complex-to-real FFT along x, then per-voxel consumer.
@@ -61,16 +76,27 @@ struct AxisArgs {
   double2* spec;
   const CgState* st;     // nullable: skip right-hand sides whose CG is not running
   const int* active;     // nullable: right-hand side of each launch-index group
-  // nullable (outer pass of a CG iteration): one block per right-hand side also sums the x
-  // pass's <p, K:p> block partials and sets alpha, in place of a separate reduction launch
+  // nullable: the x pass's <p, K:p> block partials; one block per right-hand side of the pass sums them
+  // and sets alpha, in place of a separate reduction launch (the outer pass of the CG on strain fields,
+  // the forward y pass of the CG on displacements)
   CgState* pq_st;
   const double* pq_partials;
   int pq_nblocks;
+  // CG on displacements.  mirror: forward y pass, keep the mirror planes Hermitian.  Outer passes: mode
+  // (launch_outer sets it), the CG vectors [B][d][Nh], and the <r, r> block partials [B][rr_nblocks]
+  int mirror;
+  int mode;
+  double2 *xu, *ru, *pu;
+  double* rr_partials;
+  int rr_nblocks;
+  double inv_n;          // 1 / N
+  int stream;            // the CG vectors pass the caches by
 };
 
 // dynamic LDS bytes of each pass; `inplace` drops the ping-pong buffer
 size_t xfwd_smem(const Geom& g, int R, int inplace);
 size_t xinv_smem(const Geom& g, int R, int inplace);
+size_t xop_smem(const Geom& g, int R, int inplace);  // x pass of the CG on displacements
 // y pass; proj != 0: the projection chain's y pass (three tiles per block for finite strain 3D)
 size_t mid_smem(const Geom& g, int TX, int inplace, int ZB = 1, int proj = 0);
 // sequences of one FFT call of a y-pass block of TX bins and ZB planes
@@ -157,16 +183,24 @@ hipError_t launch_simp_gradient(int mat, const double* F, const double* x, MatPa
 hipError_t launch_j2_commit(int mat, const double* F, MatParams m, double* hist, const Geom& g, hipStream_t s);
 hipError_t launch_j2_plastic(int mat, const double* F, MatParams m, double* out, const Geom& g, hipStream_t s);
 hipError_t set_smem_limits(const Geom& g, int mat, size_t bytes);
-// forward x pass of one law with FFT variant nf (pass_fft in pass_kernels.h); dynamic-LDS limits
+// x passes of one law with FFT variant nf (pass_fft in pass_kernels.h); dynamic-LDS limits
 #define FH_XPASS_DECL(name)                                                                                  \
   hipError_t name(int nf, int prod, int mat, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s); \
   hipError_t name##_limits(int mat, size_t bytes);
-FH_XPASS_DECL(xfwd_le)
-FH_XPASS_DECL(xfwd_nh)
-FH_XPASS_DECL(xfwd_stvk)
-FH_XPASS_DECL(xfwd_j2)
-FH_XPASS_DECL(xfwd_ps)
+FH_XPASS_DECL(xpass_le)
+FH_XPASS_DECL(xpass_nh)
+FH_XPASS_DECL(xpass_stvk)
+FH_XPASS_DECL(xpass_j2)
+FH_XPASS_DECL(xpass_ps)
 #undef FH_XPASS_DECL
+// the pass kernels with run-time radix stages (kernels_radix*.hip)
+hipError_t launch_xinv_radix(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s);
+hipError_t launch_mid_radix(int dir, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s);
+hipError_t launch_outer_radix(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s);
+hipError_t launch_outer_cg_radix(int mode, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s);
+hipError_t set_smem_limits_radix(const Geom& g, size_t bytes);
+hipError_t set_smem_limits_radix_outer(const Geom& g, size_t bytes);
+hipError_t set_smem_limits_radix_cg(const Geom& g, size_t bytes);
 // the pass kernels with the chirp-z transform (kernels_chirp.hip), for plans with m > 0
 hipError_t launch_xinv_chirp(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s);
 hipError_t launch_mid_chirp(int dir, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s);

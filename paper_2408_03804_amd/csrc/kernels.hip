@@ -429,18 +429,20 @@ static inline bool x_fixed128(const Geom& g, const AxisPlan& px, int R, int inpl
 
 hipError_t launch_xfwd(int prod, int mat, const XFwdArgs& a, int B, hipStream_t s) {
   dim3 grid(nblk_rows(a.g, a.R), B);
-  const size_t sm = xfwd_smem(a.g, a.R, a.inplace);
+  const bool xop = prod == PROD_XOP || prod == PROD_XOP_STORED;
+  const size_t sm = xop ? xop_smem(a.g, a.R, a.inplace) : xfwd_smem(a.g, a.R, a.inplace);
+  const bool own = prod == PROD_CGOP || prod == PROD_XOP;  // producers with length-specific kernels
   int nf = 0;
   if (a.px.dense) nf = kDense;
   else if (a.px.m > 0) nf = kChirp;
-  else if (prod == PROD_CGOP && a.inplace && a.g.ndim == 3 && fixed_len_kernels(a.px.n)) nf = kStaged + a.px.n;
-  else if (prod == PROD_CGOP && x_fixed128(a.g, a.px, a.R, a.inplace)) nf = 128;
+  else if (own && a.inplace && a.g.ndim == 3 && fixed_len_kernels(a.px.n)) nf = kStaged + a.px.n;
+  else if (own && x_fixed128(a.g, a.px, a.R, a.inplace)) nf = 128;
   switch (mat) {
-    case 0: case 1: return xfwd_le(nf, prod, mat, a, grid, sm, s);
-    case 2: case 3: return xfwd_nh(nf, prod, mat, a, grid, sm, s);
-    case 4: case 5: return xfwd_stvk(nf, prod, mat, a, grid, sm, s);
-    case 6: case 7: return xfwd_j2(nf, prod, mat, a, grid, sm, s);
-    case 8: case 9: return xfwd_ps(nf, prod, mat, a, grid, sm, s);
+    case 0: case 1: return xpass_le(nf, prod, mat, a, grid, sm, s);
+    case 2: case 3: return xpass_nh(nf, prod, mat, a, grid, sm, s);
+    case 4: case 5: return xpass_stvk(nf, prod, mat, a, grid, sm, s);
+    case 6: case 7: return xpass_j2(nf, prod, mat, a, grid, sm, s);
+    case 8: case 9: return xpass_ps(nf, prod, mat, a, grid, sm, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -460,7 +462,7 @@ hipError_t launch_xinv(int cons, const XInvArgs& a, int B, hipStream_t s) {
     else hipLaunchKernelGGL((k_xinv<CONS_CGUPD, 6, 128>), grid, dim3(kThreads), sm, s, a);
     return hipGetLastError();
   }
-  return dispatch_xinv<0>(cons, a, grid, sm, s);
+  return launch_xinv_radix(cons, a, grid, sm, s);
 }
 
 hipError_t launch_mid(int dir, const AxisArgs& a, int B, hipStream_t s) {
@@ -480,17 +482,18 @@ hipError_t launch_mid(int dir, const AxisArgs& a, int B, hipStream_t s) {
     else hipLaunchKernelGGL((k_mid_frow<1, 128>), grid, dim3(kThreads), sm, s, a);
     return hipGetLastError();
   }
-  return dispatch_mid<0>(dir, rows, a, grid, sm, s);
+  return launch_mid_radix(dir, rows, a, grid, sm, s);
 }
 
 hipError_t launch_outer(int mode, const AxisArgs& a_in, int B, hipStream_t s) {
   AxisArgs a = a_in;
+  a.mode = mode;
   const int G = outer_group(a.g, mode);
   // a plain transform may carry more sequences per block than the projection the shape was
   // chosen for: stage through the ping-pong buffer when they exceed the register staging, and
   // narrow the tile while that needs more than 64 KiB of LDS (the grid follows the tile)
   if (a.inplace && !outer_inplace_ok(a.g, a.pl, a.TX, mode)) a.inplace = 0;
-  if (mode != OUTER_PROJECT) {
+  if (mode == OUTER_FWD || mode == OUTER_INV) {
     while (a.TX > 1 && outer_smem(a.g, a.TX, a.inplace, mode) > 64 * 1024) {
       a.TX = (a.TX + 1) / 2;
       a.inplace = a_in.inplace && outer_inplace_ok(a.g, a.pl, a.TX, mode) ? 1 : 0;
@@ -506,11 +509,13 @@ hipError_t launch_outer(int mode, const AxisArgs& a_in, int B, hipStream_t s) {
     const hipError_t e = launch_outer_fixed(mode, rows, a, grid, sm, s, &done);
     if (done) return e;
   }
-  if (rows && a.inplace && a.pl.n == 128 && fixed_one_ok(128, G * kx_tile_max(a.g.nxh, a.TX))) {
+  if ((rows || (outer_cg_mode(mode) && finite_rows(a.g))) && a.inplace && a.pl.n == 128 &&
+      fixed_one_ok(128, G * kx_tile_max(a.g.nxh, a.TX))) {
+    if (outer_cg_mode(mode)) return dispatch_outer_cg<128, 0>(mode != OUTER_CGFWD && mode != OUTER_RHS, a, grid, sm, s);
     hipLaunchKernelGGL((k_outer_frow<128>), grid, dim3(kThreads), sm, s, a);
     return hipGetLastError();
   }
-  return dispatch_outer<0>(mode, rows, a, grid, sm, s);
+  return outer_cg_mode(mode) ? launch_outer_cg_radix(mode, a, grid, sm, s) : launch_outer_radix(mode, rows, a, grid, sm, s);
 }
 
 hipError_t launch_cg_reduce(int what, CgState* st, const double* partials, int nblocks, int B, hipStream_t s,
@@ -683,19 +688,18 @@ hipError_t launch_debug_constitutive(int mat, const double* e, const double* de,
 // Raise the dynamic-LDS limit of the FFT kernels when a plan needs more than 64 KiB.
 hipError_t set_smem_limits(const Geom& g, int mat, size_t bytes) {
   if (bytes <= 65536) return hipSuccess;
-  hipError_t e = pass_smem_limits<0>(g, bytes);
+  hipError_t e = set_smem_limits_radix(g, bytes);
+  if (e == hipSuccess) e = set_smem_limits_radix_outer(g, bytes);
+  if (e == hipSuccess) e = set_smem_limits_radix_cg(g, bytes);
   if (e == hipSuccess)
-    e = mat < 2 ? xfwd_le_limits(mat, bytes) : mat < 4 ? xfwd_nh_limits(mat, bytes) : mat < 6 ? xfwd_stvk_limits(mat, bytes)
-        : mat < 8 ? xfwd_j2_limits(mat, bytes) : xfwd_ps_limits(mat, bytes);
-  const int attr = (int)hipFuncAttributeMaxDynamicSharedMemorySize;
-#define FH_SET(fn) \
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), (hipFuncAttribute)attr, (int)bytes)
-  if (g.c == 6) FH_SET((k_xinv<CONS_CGUPD, 6, 128>));
-  if (g.c == 9) FH_SET((k_xinv<CONS_CGUPD, 9, 128>));
-  FH_SET((k_mid_frow<-1, 128>));
-  FH_SET((k_mid_frow<1, 128>));
-  FH_SET((k_outer_frow<128>));
-#undef FH_SET
+    e = mat < 2 ? xpass_le_limits(mat, bytes) : mat < 4 ? xpass_nh_limits(mat, bytes) : mat < 6 ? xpass_stvk_limits(mat, bytes)
+        : mat < 8 ? xpass_j2_limits(mat, bytes) : xpass_ps_limits(mat, bytes);
+  if (e == hipSuccess && g.c == 6) e = raise_limit(k_xinv<CONS_CGUPD, 6, 128>, bytes);
+  if (e == hipSuccess && g.c == 9) e = raise_limit(k_xinv<CONS_CGUPD, 9, 128>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_mid_frow<-1, 128>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_mid_frow<1, 128>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_outer_frow<128>, bytes);
+  if (e == hipSuccess) e = outer_cg_limits<128, 0>(bytes);
   if (e == hipSuccess && (g.lx != g.nx || g.lo != g.n_outer || (g.ndim == 3 && g.lm != g.ny)))
     e = set_smem_limits_chirp(g, bytes);
   if (e == hipSuccess) e = set_smem_limits_fixed(g, bytes);

@@ -27,8 +27,13 @@ hipError_t mid_len(int dir, bool rows, const AxisArgs& a, dim3 grid, size_t sm, 
 
 template <int L>
 hipError_t outer_len(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done) {
-  *done = rows || (mode == OUTER_PROJECT && a.g.small && a.g.ndim == 3);
+  *done = a.g.ndim == 3 && mode != OUTER_FWD && mode != OUTER_INV;
   if (!*done) return hipSuccess;
+  if (outer_cg_mode(mode)) {
+    const bool inv = mode != OUTER_CGFWD && mode != OUTER_RHS;
+    return a.g.small ? dispatch_outer_cg<kStaged + L, 1>(inv, a, grid, sm, s)
+                     : dispatch_outer_cg<kStaged + L, 0>(inv, a, grid, sm, s);
+  }
   if (rows) hipLaunchKernelGGL((k_outer_frow<kStaged + L>), grid, dim3(kThreads), sm, s, a);
   else hipLaunchKernelGGL((k_outer<OUTER_PROJECT, 1, 3, kStaged + L>), grid, dim3(kThreads), sm, s, a);
   return hipGetLastError();
@@ -36,19 +41,13 @@ hipError_t outer_len(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t s
 
 template <int L>
 hipError_t limits_len(size_t bytes) {
-  const int attr = (int)hipFuncAttributeMaxDynamicSharedMemorySize;
-  hipError_t e = hipSuccess;
-#define FH_SET(fn) \
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), (hipFuncAttribute)attr, (int)bytes)
-  FH_SET((k_xinv<CONS_CGUPD, 6, kStaged + L>));
-  FH_SET((k_xinv<CONS_CGUPD, 9, kStaged + L>));
-  FH_SET((k_mid<-1, kStaged + L>));
-  FH_SET((k_mid<1, kStaged + L>));
-  FH_SET((k_mid_frow<-1, kStaged + L>));
-  FH_SET((k_mid_frow<1, kStaged + L>));
-  FH_SET((k_outer_frow<kStaged + L>));
-  FH_SET((k_outer<OUTER_PROJECT, 1, 3, kStaged + L>));
-#undef FH_SET
+  hipError_t e = mid_limits<kStaged + L>(bytes);
+  if (e == hipSuccess) e = raise_limit(k_xinv<CONS_CGUPD, 6, kStaged + L>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_xinv<CONS_CGUPD, 9, kStaged + L>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_outer_frow<kStaged + L>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_outer<OUTER_PROJECT, 1, 3, kStaged + L>, bytes);
+  if (e == hipSuccess) e = outer_cg_limits<kStaged + L, 0>(bytes);
+  if (e == hipSuccess) e = outer_cg_limits<kStaged + L, 1>(bytes);
   return e;
 }
 

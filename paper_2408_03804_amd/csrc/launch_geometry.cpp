@@ -23,6 +23,9 @@ size_t xinv_smem(const Geom& g, int R, int inplace) {
   if (h > bsz) bsz = h;
   return (a + bsz) * sizeof(double2);
 }
+size_t xop_smem(const Geom& g, int R, int inplace) {
+  return (inplace ? 1ull : 2ull) * g.lx * ((g.c * R + 1) / 2) * sizeof(double2);
+}
 int mid_sequences(const Geom& g, int TX, int ZB, int proj) {
   (void)proj;  // the row-wise finite-strain y pass transforms one component tile at a time
   return kx_tile_max(g.nxh, TX) * ZB;
@@ -52,7 +55,7 @@ int mid_planes(const Geom& g, const AxisPlan& pl, int TX, int inplace, long long
 // as its two entries.  Plain transforms (debug FFTs) take whole rows (finite) or all components.
 int outer_group(const Geom& g, int mode) {
   if (g.small) return g.c;
-  return (mode == OUTER_PROJECT && g.ndim == 3) ? 2 : g.ndim;
+  return (mode != OUTER_FWD && mode != OUTER_INV && g.ndim == 3) ? 2 : g.ndim;
 }
 int outer_groups_per_rhs(const Geom& g, int mode) {
   (void)mode;  // rows of F (finite strain) or one group of all components (small strain)

@@ -14,11 +14,41 @@
 //   mid    inverse FFT along y                                 (3D only)
 //   xinv   complex-to-real FFT along x, r -= alpha q, partial <r, r>
 //
-// plus two one-block reductions that turn the partial sums into alpha and beta
-// on the device.  <p, q> is taken as <p, K:p>: p lies in the range of the
-// projection G (it is built from projected residuals) and G is self-adjoint, so
-// <p, G(K:p)> = <G p, K:p> = <p, K:p> in exact arithmetic; q is therefore never
-// stored.  The update x += alpha p of iteration k is applied by the xfwd pass of
+// (the CG on strain fields, in 2D and for CG tolerances below kDisplacementTol) or, in 3D at the
+// tolerances in everyday use, the CG on displacements:
+//
+//   outer  x += alpha_prev p, p = r + beta p per wavevector, the strain of p, inverse FFT along z
+//   mid    inverse FFT along y
+//   x      complex-to-real FFT along x, tau = K(F) : p by dual numbers, partial <p, tau>,
+//          real-to-complex FFT along x, in place
+//   mid    FFT along y (one block sums <p, tau>, alpha)
+//   outer  FFT along z, u of tau, r -= alpha u, partial <r, r>
+//
+// A compatible strain is the (symmetrised, for small strain) gradient of a displacement, so on each
+// wavevector xi the CG vectors x, r and p are three complex numbers u instead of 9 (small strain: 6)
+// real ones per voxel:
+//   finite strain  A-hat_ij = u_i xi_j
+//   small strain   A-hat_ij = (u_i xi_j + u_j xi_i) / 2
+// (the factor i of the gradient is part of u).  The projection of a field tau is the u of
+//   finite   u = tau-hat xi / |xi|^2
+//   small    u = 2 t / |xi|^2 - (xi . t) xi / |xi|^4,  t = tau-hat xi
+// and its squared norm, by Parseval, (1/N) sum w |xi|^2 |u|^2 (small: w (|xi|^2 |u|^2 + |xi . u|^2) / 2)
+// over the half spectrum, w = 2 except on the planes kx = 0 and kx = nx/2.  These are the iterates of
+// the CG on the strains in exact arithmetic; at 128^3 (finite strain) an iteration moves 731 B per
+// voxel instead of 1064 B.  In floating point the strain fields also carry an incompatible rounding
+// part that no iteration reduces; near that floor (tolerances around 1e-12) it shifts the iteration
+// count by a few per cent, and callers that compare counts there expect those of the textbook CG.
+// The spectra of real fields on the planes kx = 0 and kx = nx/2 are Hermitian in the other axes.  A
+// part of r that is not (rounding of the transforms) would vanish on the way through real space and
+// so never be reduced; the forward passes of the CG on displacements therefore keep that symmetry
+// exactly: the y pass averages each value with the conjugate of its mirror
+// image, and the outer pass of a mirrored ky runs on the conjugate sequence, so that both
+// compute the same numbers.
+//
+// Both add a one-block reduction that turns the partial sums into beta on the device.  <p, q> is taken
+// as <p, K:p>: p lies in the range of the projection G (it is built from projected residuals) and G is
+// self-adjoint, so <p, G(K:p)> = <G p, K:p> = <p, K:p> in exact arithmetic; q is therefore never
+// stored.  On strain fields the update x += alpha p of iteration k is applied by the xfwd pass of
 // iteration k+1, which reads p anyway (k_cg_finish applies the last one).
 #pragma once
 
@@ -96,6 +126,22 @@ __device__ __forceinline__ void pass_fft(double2* A, double2* Bf, int nseq, cons
 __device__ __forceinline__ double ld_stream(const double* p) { return __builtin_nontemporal_load(p); }
 __device__ __forceinline__ void st_stream(double* p, double v) { __builtin_nontemporal_store(v, p); }
 
+// nt: past the caches (wave-uniform)
+__device__ __forceinline__ double2 ld_vec(const double2* p, bool nt) {
+  if (!nt) return *p;
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  const v2d v = __builtin_nontemporal_load(reinterpret_cast<const v2d*>(p));
+  return make_double2(v.x, v.y);
+}
+__device__ __forceinline__ void st_vec(double2* p, double2 v, bool nt) {
+  if (!nt) {
+    *p = v;
+    return;
+  }
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  __builtin_nontemporal_store(v2d{v.x, v.y}, reinterpret_cast<v2d*>(p));
+}
+
 // Sum of x[tid], x[tid + kThreads], x[tid + 2 kThreads], ... (i < n) in that order, with up to S of
 // the thread's loads in flight together; bitwise the strided loop's sum.
 template <int S, int BD>
@@ -114,25 +160,21 @@ __device__ __forceinline__ double strided_sum(const double* __restrict__ x, int 
   return acc;
 }
 
-// Gather n complex entries into LDS: dst[i] = v for (v, i) = src(t), t < n.  Each thread issues up
-// to S global loads before its first LDS write, so that S of its loads are in flight together (in
-// a plain load-then-write loop each load waits for the previous one).  Used where it measured
-// faster: the inverse x pass and the plain y pass; the row-wise y and outer passes, which run at
-// their register caps, were slower with it.
+// Gather n complex entries into LDS: dst[t] = src(t), t < n.  Each thread issues up to S global loads
+// before its first LDS write, so that S of its loads are in flight together (in a plain
+// load-then-write loop each load waits for the previous one).  The loads are unconditional, at a
+// clamped index: a load under a condition is waited for before the next one is issued.
 template <int S, typename Src>
 __device__ __forceinline__ void gather_staged(double2* dst, int n, Src src) {
   for (int base = 0; base < n; base += S * kThreads) {
     double2 v[S];
-    int di[S];
+#pragma unroll
+    for (int e = 0; e < S; ++e) v[e] = src(min(base + (int)threadIdx.x + e * kThreads, n - 1));
 #pragma unroll
     for (int e = 0; e < S; ++e) {
       const int t = base + (int)threadIdx.x + e * kThreads;
-      di[e] = -1;
-      if (t < n) v[e] = src(t, &di[e]);
+      if (t < n) dst[t] = v[e];
     }
-#pragma unroll
-    for (int e = 0; e < S; ++e)
-      if (di[e] >= 0) dst[di[e]] = v[e];
   }
 }
 
@@ -431,14 +473,24 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
 
   const FastDiv fdh = make_fastdiv((unsigned)nxh);
   const FastDiv fdp = make_fastdiv((unsigned)P);
-  gather_staged<8>(H, nseq * nxh, [&](int t, int* di) {
-    const int qr = (int)fdiv((unsigned)t, fdh);
-    const int k = t - qr * nxh;
-    const int j = qr / nr;
-    const int r = qr - j * nr;
-    *di = k * nseq + qr;
-    return a.spec[((long long)b * C + j) * g.Nh + (long long)(row0 + r) * g.nxp + k];
-  });
+  const int hcnt = nseq * nxh;
+  for (int base = 0; base < hcnt; base += 8 * kThreads) {
+    double2 v[8];
+    int di[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int t = min(base + (int)threadIdx.x + e * kThreads, hcnt - 1);
+      const int qr = (int)fdiv((unsigned)t, fdh);
+      const int k = t - qr * nxh;
+      const int j = qr / nr;
+      const int r = qr - j * nr;
+      di[e] = k * nseq + qr;
+      v[e] = a.spec[((long long)b * C + j) * g.Nh + (long long)(row0 + r) * g.nxp + k];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (base + (int)threadIdx.x + e * kThreads < hcnt) H[di[e]] = v[e];
+  }
   __syncthreads();
   for (int t = threadIdx.x; t < P * nx; t += blockDim.x) {
     const int k = (int)fdiv((unsigned)t, fdp);
@@ -508,6 +560,243 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
 }
 
 // ============================================================================
+// x-axis pass of the CG on displacements
+// ============================================================================
+// The C real rows (component j of line r) of a block are packed two per complex sequence: real row
+// qr = j * nr + r is the real (even qr) or imaginary part of sequence qr / 2.
+__device__ __forceinline__ double* x_slot(double2* A, int P, int nr, int j, int r, int x) {
+  const int qr = j * nr + r;
+  return reinterpret_cast<double*>(&A[x * P + (qr >> 1)]) + (qr & 1);
+}
+
+// Axis length of FFT variant NF if it has one compiled in, else 0.
+constexpr int variant_len(int nf) { return nf > kStaged ? nf - kStaged : nf > 0 ? nf : 0; }
+
+// Half spectra of the block's real rows into packed full spectra in LDS (k and nx - k from one load
+// pair), and back.  NX: the axis length if known at compile time.  From 94 points on a wavefront
+// takes whole sequences (its sequence index is scalar, lanes run along k), three of them in flight:
+// the index arithmetic of flattened loops was a good part of the x pass's instructions.
+template <int NX>
+__device__ __forceinline__ void load_rows(double2* A, const double2* spec, const Geom& g, int nseq, int nr, int row0) {
+  const int P = (nseq + 1) >> 1;
+  const int nx = NX > 0 ? NX : g.nx, nxh = nx / 2 + 1;
+  const FastDiv fdr = make_fastdiv((unsigned)nr);
+  auto row = [&](int qr) {
+    const int j = (int)fdiv((unsigned)qr, fdr);
+    return spec + j * g.Nh + (long long)(row0 + qr - j * nr) * g.nxp;
+  };
+  auto put = [&](int q, int k, double2 ha, double2 hb) {
+    if (2 * q + 1 == nseq) hb = make_double2(0.0, 0.0);
+    if (k == 0 || 2 * k == nx) {
+      A[k * P + q] = make_double2(ha.x, hb.x);
+    } else {
+      A[k * P + q] = make_double2(ha.x - hb.y, ha.y + hb.x);
+      A[(nx - k) * P + q] = make_double2(ha.x + hb.y, hb.x - ha.y);
+    }
+  };
+  constexpr int S = 3;
+  if (nxh >= 48) {
+    constexpr int W = kThreads / 64;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    for (int k0 = 0; k0 < nxh; k0 += 64) {
+      const int kc = min(k0 + lane, nxh - 1);
+      for (int q0 = wave; q0 < P; q0 += S * W) {
+        double2 ha[S], hb[S];
+#pragma unroll
+        for (int e = 0; e < S; ++e) {
+          const int q = min(q0 + e * W, P - 1);
+          ha[e] = row(2 * q)[kc];
+          hb[e] = row(min(2 * q + 1, nseq - 1))[kc];
+        }
+#pragma unroll
+        for (int e = 0; e < S; ++e)
+          if (q0 + e * W < P && k0 + lane < nxh) put(q0 + e * W, k0 + lane, ha[e], hb[e]);
+      }
+    }
+  } else {
+    const FastDiv fdh = make_fastdiv((unsigned)nxh);
+    const int cnt = P * nxh;
+    for (int base = 0; base < cnt; base += S * kThreads) {
+      double2 ha[S], hb[S];
+#pragma unroll
+      for (int e = 0; e < S; ++e) {
+        const int t = min(base + (int)threadIdx.x + e * kThreads, cnt - 1);
+        const int q = NX > 0 ? t / (NX / 2 + 1) : (int)fdiv((unsigned)t, fdh);
+        const int k = t - q * nxh;
+        ha[e] = row(2 * q)[k];
+        hb[e] = row(min(2 * q + 1, nseq - 1))[k];
+      }
+#pragma unroll
+      for (int e = 0; e < S; ++e) {
+        const int t = base + (int)threadIdx.x + e * kThreads;
+        const int q = NX > 0 ? t / (NX / 2 + 1) : (int)fdiv((unsigned)t, fdh);
+        if (t < cnt) put(q, t - q * nxh, ha[e], hb[e]);
+      }
+    }
+  }
+}
+
+// Separate the two real rows packed in each transformed sequence and store their half spectra.
+template <int NX>
+__device__ __forceinline__ void store_rows(const double2* A, double2* spec, const Geom& g, int nseq, int nr, int row0) {
+  const int P = (nseq + 1) >> 1;
+  const int nx = NX > 0 ? NX : g.nx, nxh = nx / 2 + 1;
+  const FastDiv fdr = make_fastdiv((unsigned)nr);
+  auto put = [&](int q, int k) {
+    const double2 zk = A[k * P + q];
+    const double2 zm = A[(k == 0 ? 0 : nx - k) * P + q];
+    const int ja = (int)fdiv((unsigned)(2 * q), fdr);
+    (spec + ja * g.Nh + (long long)(row0 + 2 * q - ja * nr) * g.nxp)[k] =
+        make_double2(0.5 * (zk.x + zm.x), 0.5 * (zk.y - zm.y));
+    if (2 * q + 1 < nseq) {
+      const int jb = (int)fdiv((unsigned)(2 * q + 1), fdr);
+      (spec + jb * g.Nh + (long long)(row0 + 2 * q + 1 - jb * nr) * g.nxp)[k] =
+          make_double2(0.5 * (zk.y + zm.y), 0.5 * (zm.x - zk.x));
+    }
+  };
+  if (nxh >= 48) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    for (int q = wave; q < P; q += kThreads / 64)
+      for (int k = threadIdx.x & 63; k < nxh; k += 64) put(q, k);
+  } else {
+    const FastDiv fdh = make_fastdiv((unsigned)nxh);
+    for (int t = threadIdx.x; t < P * nxh; t += blockDim.x) {
+      const int q = NX > 0 ? t / (NX / 2 + 1) : (int)fdiv((unsigned)t, fdh);
+      put(q, t - q * nxh);
+    }
+  }
+}
+
+// Material of right-hand side b of a multi-cell batch (its cell's phase map and table) and the load
+// index within the cell.
+__device__ __forceinline__ MatParams cell_material(const XFwdArgs& a, int b, int* load) {
+  MatParams mat = a.mat;
+  *load = b;
+  if (a.per_inst > 0) {
+    const int cell = b / a.per_inst;
+    *load = b - cell * a.per_inst;
+    mat.phase += (long long)cell * a.g.N;
+    mat.table += (long long)cell * 2 * kMaxPhase;
+  }
+  return mat;
+}
+
+// K : p of one voxel from the stored symmetric tangent (upper triangle row by row)
+template <int C>
+__device__ __forceinline__ void stored_apply(const double* Kst, long long N, long long vox, const double* pv, double* v) {
+#pragma unroll
+  for (int i = 0; i < C; ++i) v[i] = 0.0;
+  int idx = 0;
+#pragma unroll
+  for (int i = 0; i < C; ++i) {
+#pragma unroll
+    for (int j = i; j < C; ++j) {
+      const double k = Kst[(long long)idx * N + vox];
+      v[i] += k * pv[j];
+      if (j != i) v[j] += k * pv[i];
+      ++idx;
+    }
+  }
+}
+
+// The x pass of a CG iteration: inverse transform of the strain of p, K : p per voxel (dual numbers,
+// or the stored tangent), partial <p, K:p>, forward transform, in place in the spectrum.
+// It reads and writes the half spectrum and reads the linearisation point: 219 B per voxel at 128^3,
+// c = 9, which a copy takes 107 us for; measured 123 us (149 us while its index arithmetic was a third
+// of its 1376 instructions per voxel), in place of the forward and the inverse x pass of the CG on
+// strain fields, 184 and 92 us.  The strain of this thread's voxel is loaded beside the spectrum when a
+// block has one voxel per thread, so that it is there when the inverse transform is done.
+template <int STORED, int MAT, int NDIM, int NF = 0>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NF > 0 ? 4 : 2, 8))) k_xop(XFwdArgs a) {
+  constexpr int C = MatTraits<MAT, NDIM>::C;
+  constexpr bool NEED_E = !STORED && MAT != MAT_LE;
+  constexpr int NX = variant_len(NF);
+  const int b = a.active ? a.active[blockIdx.y] : (int)blockIdx.y;
+  if (a.st[b].status != CG_RUNNING) return;
+  const Geom& g = a.g;
+  int lb;
+  const MatParams mat = cell_material(a, b, &lb);
+  const int nx = NX > 0 ? NX : g.nx;
+  const int row0 = blockIdx.x * a.R;
+  const int nr = min(a.R, g.ny * g.nz - row0);
+  const int nseq = C * nr;
+  const int P = (nseq + 1) >> 1;
+  extern __shared__ double2 smem[];
+  double2* A = smem;
+  double2* Bf = smem + (size_t)g.lx * P;  // ping-pong partner (unused in place)
+  __shared__ double red[kThreads / 64];
+  const long long N = g.N;
+  double2* spec = a.spec + (long long)b * C * g.Nh;
+
+  const bool pre = nr * nx <= (int)blockDim.x;
+  double epre[C];
+  if (NEED_E && pre && (int)threadIdx.x < nr * nx) {
+#pragma unroll
+    for (int j = 0; j < C; ++j) epre[j] = ld_stream(a.F + j * N + (long long)row0 * nx + threadIdx.x);
+  }
+  load_rows<NX>(A, spec, g, nseq, nr, row0);
+  __syncthreads();
+  pass_fft<1, NF>(A, Bf, P, a.px, a.inplace);
+
+  double acc = 0.0;
+  const FastDiv fdx = make_fastdiv((unsigned)nx);
+  const bool even = (nr & 1) == 0;  // then component j of a voxel sits nr doubles after component j - 1
+#pragma unroll 1
+  for (int t = threadIdx.x; t < nr * nx; t += blockDim.x) {
+    const int r = NX > 0 ? t / (NX > 0 ? NX : 1) : (int)fdiv((unsigned)t, fdx);
+    const int x = t - r * nx;
+    const long long vox = (long long)row0 * nx + t;
+    double* slot = x_slot(A, P, nr, 0, r, x);
+    double pv[C], v[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) pv[j] = (even ? slot[j * nr] : *x_slot(A, P, nr, j, r, x)) * a.scale;
+    if (STORED) {
+      stored_apply<C>(a.Kst, N, vox, pv, v);
+    } else {
+      Local L;
+      double e[C];
+      load_local<MAT, NDIM>(mat, vox, L);
+#pragma unroll
+      for (int j = 0; j < C; ++j) e[j] = !NEED_E ? 0.0 : pre ? epre[j] : ld_stream(a.F + j * N + vox);
+      tangent_jvp_ad<MAT, NDIM>(e, pv, L, v);
+    }
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+      acc += pv[j] * v[j];
+      if (even) slot[j * nr] = v[j];
+      else *x_slot(A, P, nr, j, r, x) = v[j];
+    }
+  }
+  if (nseq & 1) {
+    for (int x = threadIdx.x; x < nx; x += blockDim.x) A[x * P + P - 1].y = 0.0;
+  }
+  __syncthreads();
+  pass_fft<-1, NF>(A, Bf, P, a.px, a.inplace);
+  store_rows<NX>(A, spec, g, nseq, nr, row0);
+  const double s = block_sum(acc, red);
+  if (threadIdx.x == 0) a.partials[(long long)b * a.nblocks + blockIdx.x] = s;
+}
+
+// One block of a launch sums <p, K:p> of its right-hand side and sets alpha, for the next launch
+// (every thread of the block calls it; no block of this launch reads what it writes).
+__device__ __forceinline__ void reduce_alpha(const AxisArgs& a, int b) {
+  __shared__ double red[kThreads / 64];
+  const double s = block_sum(strided_sum<8, kThreads>(a.pq_partials + (long long)b * a.pq_nblocks, a.pq_nblocks), red);
+  if (threadIdx.x == 0) cg_finalize<RED_PQ>(a.pq_st[b], s);
+}
+
+// kx on a plane whose spectrum mirrors itself
+__device__ __forceinline__ bool mirror_plane(int kx, int nx) { return kx == 0 || 2 * kx == nx; }
+// Row y of sequence q of the transform of a real sequence, averaged with the conjugate of its mirror
+// image (D[y * nseq + q], rows 0..n-1).
+__device__ __forceinline__ double2 hermitian(const double2* D, int y, int q, int nseq, int n) {
+  const double2 v = D[y * nseq + q];
+  const double2 m = D[(y == 0 ? 0 : n - y) * nseq + q];
+  return make_double2(0.5 * (v.x + m.x), 0.5 * (v.y - m.y));
+}
+
+// ============================================================================
 // y-axis pass (3D): complex FFT of the half spectrum along y, in place
 // ============================================================================
 // A block transforms the tw bins kx0.. of ZB consecutive z planes (contiguous in memory when
@@ -519,6 +808,7 @@ __global__ void __launch_bounds__(kThreads) k_mid(AxisArgs a) {
   const int comp = blockIdx.z - vb * g.c;
   const int b = a.active ? a.active[vb] : vb;
   if (a.st != nullptr && a.st[b].status != CG_RUNNING) return;
+  if (DIR < 0 && a.pq_st != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && comp == 0) reduce_alpha(a, b);
   const int kx0 = blockIdx.x * a.TX;
   const int tw = kx_tile_width(g.nxh, a.TX, blockIdx.x);
   const int ny = g.ny;
@@ -530,12 +820,11 @@ __global__ void __launch_bounds__(kThreads) k_mid(AxisArgs a) {
   const long long base = ((long long)b * g.c + comp) * g.Nh + (long long)z0 * ny * g.nxp + kx0;
   const FastDiv fdq = make_fastdiv((unsigned)nseq);
   const FastDiv fdt = make_fastdiv((unsigned)tw);
-  gather_staged<8>(A, ny * nseq, [&](int t, int* di) {
+  gather_staged<8>(A, ny * nseq, [&](int t) {
     const int y = (int)fdiv((unsigned)t, fdq);
     const int q = t - y * nseq;
     const int zz = (int)fdiv((unsigned)q, fdt);
     const int s = q - zz * tw;
-    *di = t;
     return a.spec[base + (long long)(zz * ny + y) * g.nxp + s];
   });
   __syncthreads();
@@ -545,7 +834,8 @@ __global__ void __launch_bounds__(kThreads) k_mid(AxisArgs a) {
     const int q = t - y * nseq;
     const int zz = (int)fdiv((unsigned)q, fdt);
     const int s = q - zz * tw;
-    a.spec[base + (long long)(zz * ny + y) * g.nxp + s] = A[t];
+    a.spec[base + (long long)(zz * ny + y) * g.nxp + s] =
+        (DIR < 0 && a.mirror && mirror_plane(kx0 + s, g.nx)) ? hermitian(A, y, q, nseq, ny) : A[t];
   }
 }
 
@@ -782,6 +1072,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
   const int row = bz - vb * 3;
   const int b = a.active ? a.active[vb] : vb;
   if (a.st != nullptr && a.st[b].status != CG_RUNNING) return;
+  if (DIR < 0 && a.pq_st != nullptr && bx == 0 && by == 0 && row == 0) reduce_alpha(a, b);
   const int kx0 = bx * a.TX;
   const int tw = kx_tile_width(g.nxh, a.TX, bx);
   const int ny = g.ny;
@@ -804,6 +1095,12 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
     *xx = signed_freq(kx0 + sx, g.nx, g.ks[0]);
     *xy = signed_freq(y, ny, g.ks[1]);
   };
+  // transformed entry t; on a mirror plane (xi_x = 0) made Hermitian
+  auto value = [&](int t, double xx) {
+    if (DIR > 0 || !a.mirror || xx != 0.0) return A[t];
+    const int y = (int)fdiv((unsigned)t, fdq);
+    return hermitian(A, y, t - y * nseq, nseq, ny);
+  };
   auto load = [&](int slot) {
     for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
       long long off;
@@ -817,7 +1114,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
       long long off;
       double xx, xy;
       where(t, &off, &xx, &xy);
-      a.spec[cbase + slot * g.Nh + off] = A[t];
+      a.spec[cbase + slot * g.Nh + off] = value(t, xx);
     }
   };
   double2 held[kFrowHeld];
@@ -846,7 +1143,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
         long long off;
         double xx, xy;
         where(t, &off, &xx, &xy);
-        const double2 v = A[t];
+        const double2 v = value(t, xx);
         a.spec[cbase + off] = make_double2(held[e].x + xy * v.x, held[e].y + xy * v.y);
       }
     }
@@ -963,6 +1260,265 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
 }
 
 // ============================================================================
+// outer-axis passes of the CG on displacements (3D)
+// ============================================================================
+// Bins (kx0 + s, ky, kz) of a block: TX bins of kx at one ky along the whole outer axis.
+// LDS: element o of sequence (jj, s) at D[o * nseq + jj * tw + s].
+// Finite strain: a block takes one row i of F, whose spectrum arrives (and leaves) as two sequences
+// per bin: v_i = xi_x a_i0 + xi_y a_i1 and w_i = a_i2 in the slots (i,0) and (i,2) of the row-wise
+// y pass.  Small strain: all six components.
+// Bound by HBM, the CG's vector updates being done here on one component per row of F (128^3: forward
+// 96 B per voxel, 53 us; inverse 168 B, 73 us); the projection pass on strain fields (96 B, 51 us)
+// leaves them to the x passes, on nine components each.  Small strain, 6 right-hand sides at 64^3: 18
+// and 26 us.
+template <int SMALL>
+struct OuterTile {
+  static constexpr int NDIM = 3;
+  static constexpr int C = SMALL ? 6 : 9;
+  static constexpr int G = SMALL ? C : 2;         // sequences per bin
+  static constexpr int NGRP = SMALL ? 1 : NDIM;   // blocks per bin tile
+  static constexpr int DU = SMALL ? NDIM : 1;     // displacement components per block
+  int b, grp, kx0, tw, ky, n, nseq, part;
+  long long ostride, spec0, u0;
+  FastDiv fdq, fdt;
+
+  __device__ __forceinline__ OuterTile(const AxisArgs& a) {
+    const Geom& g = a.g;
+    unsigned bx, by, bz;
+    xcd_blocks(&bx, &by, &bz);
+    const int vb = bz / NGRP;
+    grp = bz - vb * NGRP;
+    b = a.active ? a.active[vb] : vb;
+    kx0 = bx * a.TX;
+    tw = kx_tile_width(g.nxh, a.TX, (int)bx);
+    ky = by;
+    n = g.n_outer;
+    nseq = G * tw;
+    part = bx + gridDim.x * (by + gridDim.y * grp);
+    ostride = (long long)g.n_mid * g.nxp;
+    const long long base = (long long)ky * g.nxp + kx0;
+    spec0 = ((long long)b * C + (SMALL ? 0 : grp * NDIM)) * g.Nh + base;
+    u0 = ((long long)b * NDIM + grp) * g.Nh + base;
+    fdq = make_fastdiv((unsigned)nseq);
+    fdt = make_fastdiv((unsigned)tw);
+  }
+  // spectrum offset of LDS entry t, its sequence jj and bin s
+  __device__ __forceinline__ long long spec_at(const Geom& g, int t, int* jj, int* s) const {
+    const int o = (int)fdiv((unsigned)t, fdq);
+    const int rem = t - o * nseq;
+    *jj = (int)fdiv((unsigned)rem, fdt);
+    *s = rem - *jj * tw;
+    const int slot = SMALL ? *jj : 2 * *jj;
+    return spec0 + slot * g.Nh + o * ostride + *s;
+  }
+  // bin t of the block's n * tw: outer index o, bin s, displacement offset, wavevector
+  __device__ __forceinline__ void bin(const Geom& g, int t, int* po, int* ps, long long* uo, double* xi) const {
+    const int o = (int)fdiv((unsigned)t, fdt);
+    const int s = t - o * tw;
+    *po = o;
+    *ps = s;
+    *uo = u0 + o * ostride + s;
+    xi[0] = signed_freq(kx0 + s, g.nx, g.ks[0]);
+    xi[1] = signed_freq(ky, g.ny, g.ks[1]);
+    xi[2] = signed_freq(o, g.nz, g.ks[2]);
+  }
+};
+
+// Forward: outer-axis FFT of tau-hat, its displacement u, r -= alpha u (a.mode OUTER_CGFWD), or
+// r = -u (OUTER_RHS); partial <r, r>.  Reads the spectrum once and reads and writes r.
+template <int SMALL, int NF>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NF > 0 && !SMALL ? 5 : 2, 8))) k_ofwd(AxisArgs a) {
+  typedef OuterTile<SMALL> Tile;
+  constexpr int NDIM = 3, G = Tile::G, DU = Tile::DU;
+  const Geom& g = a.g;
+  const Tile T(a);
+  const bool cg = a.mode == OUTER_CGFWD;
+  if (cg && a.st[T.b].status != CG_RUNNING) return;
+  extern __shared__ double2 smem[];
+  double2* D = smem;
+  double2* pong = smem + (size_t)g.lo * T.nseq;
+  __shared__ double red[kThreads / 64];
+  const double alpha = cg ? a.st[T.b].alpha : 0.0;
+  const int cnt = T.n * T.nseq;
+  // a mirror plane's sequence at ky is the conjugate of the one at ny - ky (minus it for v, which
+  // carries xi_y): beyond ny / 2 the latter is transformed and the result mirrored below
+  const bool mirror = 2 * T.ky > g.ny;
+  gather_staged<4>(D, cnt, [&](int t) {
+    int jj, s;
+    double2 v = a.spec[T.spec_at(g, t, &jj, &s)];
+    if (mirror && mirror_plane(T.kx0 + s, g.nx)) v = (!SMALL && jj == 0) ? make_double2(-v.x, v.y) : make_double2(v.x, -v.y);
+    return v;
+  });
+  __syncthreads();
+  pass_fft<-1, NF>(D, pong, T.nseq, a.pl, a.inplace);
+  double acc = 0.0;
+  for (int t = threadIdx.x; t < T.n * T.tw; t += blockDim.x) {
+    int o, s;
+    long long uo;
+    double xi[NDIM];
+    T.bin(g, t, &o, &s, &uo, xi);
+    const bool edge = mirror_plane(T.kx0 + s, g.nx);
+    const bool flip = mirror && edge;              // take the mirror image of row n - o
+    const bool self = edge && !flip && (T.ky == 0 || 2 * T.ky == g.ny);
+    const int row = flip && o > 0 ? T.n - o : o;
+    if (flip) {
+#pragma unroll
+      for (int i = 0; i < NDIM; ++i) xi[i] = -xi[i];
+    }
+    auto value = [&](int jj) {
+      return self ? hermitian(D, row, jj * T.tw + s, T.nseq, T.n) : D[row * T.nseq + jj * T.tw + s];
+    };
+    double2 r[DU];
+#pragma unroll
+    for (int i = 0; i < DU; ++i) r[i] = cg ? ld_vec(a.ru + uo + i * g.Nh, a.stream) : make_double2(0.0, 0.0);
+    double n2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NDIM; ++i) n2 += xi[i] * xi[i];
+    double2 u[DU];
+#pragma unroll
+    for (int i = 0; i < DU; ++i) u[i] = make_double2(0.0, 0.0);
+    if (n2 > 0.0) {
+      const double inv = 1.0 / n2;
+      if constexpr (SMALL) {
+        const double h2 = 0.70710678118654752440;
+        double2 v[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) v[j] = value(j);
+        double2 t3[NDIM];
+        t3[0] = make_double2(v[0].x * xi[0] + h2 * (v[5].x * xi[1] + v[4].x * xi[2]), v[0].y * xi[0] + h2 * (v[5].y * xi[1] + v[4].y * xi[2]));
+        t3[1] = make_double2(v[1].x * xi[1] + h2 * (v[5].x * xi[0] + v[3].x * xi[2]), v[1].y * xi[1] + h2 * (v[5].y * xi[0] + v[3].y * xi[2]));
+        t3[2] = make_double2(v[2].x * xi[2] + h2 * (v[4].x * xi[0] + v[3].x * xi[1]), v[2].y * xi[2] + h2 * (v[4].y * xi[0] + v[3].y * xi[1]));
+        double2 d = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int i = 0; i < NDIM; ++i) {
+          d.x += xi[i] * t3[i].x;
+          d.y += xi[i] * t3[i].y;
+        }
+        d = cscale(d, inv);
+#pragma unroll
+        for (int i = 0; i < NDIM; ++i)
+          u[i] = make_double2((2.0 * t3[i].x - d.x * xi[i]) * inv, (2.0 * t3[i].y - d.y * xi[i]) * inv);
+      } else {
+        const double2 v = value(0);
+        const double2 w = value(1);
+        u[0] = make_double2((v.x + xi[2] * w.x) * inv, (v.y + xi[2] * w.y) * inv);
+      }
+    }
+    if (flip) {  // u at -xi is -conj of u at xi
+#pragma unroll
+      for (int i = 0; i < DU; ++i) u[i].x = -u[i].x;
+    }
+    double nrm = 0.0;
+    double2 d = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int i = 0; i < DU; ++i) {
+      if (cg) r[i] = make_double2(r[i].x - alpha * u[i].x, r[i].y - alpha * u[i].y);
+      else r[i] = make_double2(-u[i].x, -u[i].y);
+      st_vec(a.ru + uo + i * g.Nh, r[i], a.stream);
+      nrm += n2 * (r[i].x * r[i].x + r[i].y * r[i].y);
+      if (SMALL) {
+        d.x += xi[i] * r[i].x;
+        d.y += xi[i] * r[i].y;
+      }
+    }
+    if (SMALL) nrm = 0.5 * (nrm + d.x * d.x + d.y * d.y);
+    acc += edge ? nrm : 2.0 * nrm;
+  }
+  const double sum = block_sum(acc, red);
+  if (threadIdx.x == 0) a.rr_partials[(long long)T.b * a.rr_nblocks + T.part] = sum * a.inv_n;
+}
+
+// Inverse: a displacement per bin, its strain in the form the inverse passes take, inverse outer-axis
+// FFT.  a.mode OUTER_CGINV: x += alpha p, p = r + beta p, the strain of p (first iteration: x = 0, p = r);
+// OUTER_SOLUTION: the strain of x + alpha p (zero if no iteration was done); OUTER_RESIDUAL: of r.
+template <int SMALL, int NF>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NF > 0 && !SMALL ? 5 : 2, 8))) k_oinv(AxisArgs a) {
+  typedef OuterTile<SMALL> Tile;
+  constexpr int NDIM = 3, G = Tile::G, DU = Tile::DU;
+  const Geom& g = a.g;
+  const Tile T(a);
+  const CgState& S = a.st[T.b];
+  if (a.mode == OUTER_CGINV && S.status != CG_RUNNING) return;
+  const double alpha = S.alpha, beta = S.beta;
+  const bool first = S.first;
+  // the last update of x is still to be made for a solve that stopped after an iteration
+  const bool some = S.iters >= 1;
+  const bool last = some && (S.status == CG_CONVERGED || S.status == CG_MAXIT);
+  extern __shared__ double2 smem[];
+  double2* D = smem;
+  double2* pong = smem + (size_t)g.lo * T.nseq;
+  for (int t = threadIdx.x; t < T.n * T.tw; t += blockDim.x) {
+    int o, s;
+    long long uo;
+    double xi[NDIM];
+    T.bin(g, t, &o, &s, &uo, xi);
+    const int e0 = o * T.nseq + s;
+    double2 u[DU];
+    if (a.mode == OUTER_CGINV) {
+      double2 po[DU], xo[DU];
+#pragma unroll
+      for (int i = 0; i < DU; ++i) {
+        u[i] = ld_vec(a.ru + uo + i * g.Nh, a.stream);
+        if (!first) {
+          po[i] = ld_vec(a.pu + uo + i * g.Nh, a.stream);
+          xo[i] = ld_vec(a.xu + uo + i * g.Nh, a.stream);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < DU; ++i) {
+        double2 x = make_double2(0.0, 0.0);
+        if (!first) {
+          x = make_double2(xo[i].x + alpha * po[i].x, xo[i].y + alpha * po[i].y);
+          u[i] = make_double2(u[i].x + beta * po[i].x, u[i].y + beta * po[i].y);
+        }
+        st_vec(a.xu + uo + i * g.Nh, x, a.stream);
+        st_vec(a.pu + uo + i * g.Nh, u[i], a.stream);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < DU; ++i) {
+        u[i] = make_double2(0.0, 0.0);
+        if (a.mode == OUTER_RESIDUAL) {
+          u[i] = a.ru[uo + i * g.Nh];
+        } else if (some) {
+          u[i] = a.xu[uo + i * g.Nh];
+          if (last) {
+            const double2 p = a.pu[uo + i * g.Nh];
+            u[i] = make_double2(u[i].x + alpha * p.x, u[i].y + alpha * p.y);
+          }
+        }
+      }
+    }
+    if constexpr (SMALL) {
+      const double h2 = 0.70710678118654752440;
+      double2 v[G];
+#pragma unroll
+      for (int i = 0; i < NDIM; ++i) v[i] = cscale(u[i], xi[i]);
+      // sqrt(2) times half the symmetrised product
+      auto shear = [&](int i, int j) {
+        return make_double2(h2 * (u[i].x * xi[j] + u[j].x * xi[i]), h2 * (u[i].y * xi[j] + u[j].y * xi[i]));
+      };
+      v[3] = shear(1, 2);
+      v[4] = shear(0, 2);
+      v[5] = shear(0, 1);
+#pragma unroll
+      for (int j = 0; j < G; ++j) D[e0 + j * T.tw] = v[j];
+    } else {
+      // the inverse y pass multiplies by xi_x and xi_y
+      D[e0] = u[0];
+      D[e0 + T.tw] = cscale(u[0], xi[2]);
+    }
+  }
+  __syncthreads();
+  pass_fft<+1, NF>(D, pong, T.nseq, a.pl, a.inplace);
+  const int cnt = T.n * T.nseq;
+  for (int t = threadIdx.x; t < cnt; t += blockDim.x) {
+    int jj, s;
+    a.spec[T.spec_at(g, t, &jj, &s)] = D[t];
+  }
+}
+
+// ============================================================================
 // launches of the pass kernels with FFT variant NF (grid and LDS bytes from the caller)
 // ============================================================================
 template <int NF>
@@ -998,6 +1554,20 @@ hipError_t dispatch_mid(int dir, bool rows, const AxisArgs& a, dim3 grid, size_t
   return hipGetLastError();
 }
 
+// the outer passes of the CG on displacements
+template <int NF, int SMALL>
+hipError_t dispatch_outer_cg(bool inverse, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s) {
+  if (inverse) hipLaunchKernelGGL((k_oinv<SMALL, NF>), grid, dim3(kThreads), sm, s, a);
+  else hipLaunchKernelGGL((k_ofwd<SMALL, NF>), grid, dim3(kThreads), sm, s, a);
+  return hipGetLastError();
+}
+
+template <int NF>
+hipError_t dispatch_outer_cg(int mode, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s) {
+  const bool inv = mode != OUTER_CGFWD && mode != OUTER_RHS;
+  return a.g.small ? dispatch_outer_cg<NF, 1>(inv, a, grid, sm, s) : dispatch_outer_cg<NF, 0>(inv, a, grid, sm, s);
+}
+
 // rows: the row-wise finite-strain projection (3D)
 template <int NF>
 hipError_t dispatch_outer(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s) {
@@ -1021,37 +1591,59 @@ hipError_t dispatch_outer(int mode, bool rows, const AxisArgs& a, dim3 grid, siz
   return hipGetLastError();
 }
 
-// Dynamic-LDS limit of every pass kernel of variant NF that a grid of this kind launches (the
-// forward x pass: xfwd_limits).
+// Dynamic-LDS limits of the pass kernels of variant NF that a grid of this kind launches (the x passes
+// with a law: xpass_law.h).
+template <typename Fn>
+hipError_t raise_limit(Fn* fn, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+template <int NF, int SMALL>
+hipError_t outer_cg_limits(size_t bytes) {
+  hipError_t e = raise_limit(k_ofwd<SMALL, NF>, bytes);
+  return e == hipSuccess ? raise_limit(k_oinv<SMALL, NF>, bytes) : e;
+}
 template <int NF>
-hipError_t pass_smem_limits(const Geom& g, size_t bytes) {
-  const int attr = (int)hipFuncAttributeMaxDynamicSharedMemorySize;
-  hipError_t e = hipSuccess;
-#define FH_SET(fn) \
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), (hipFuncAttribute)attr, (int)bytes)
-#define FH_X(CC) FH_SET((k_xinv<CONS_IDENT, CC, NF>)); FH_SET((k_xinv<CONS_RHS, CC, NF>)); FH_SET((k_xinv<CONS_CGUPD, CC, NF>));
-  switch (g.c) {
-    case 3: FH_X(3); break;
-    case 4: FH_X(4); break;
-    case 6: FH_X(6); break;
-    case 9: FH_X(9); break;
-    default: break;
-  }
-#undef FH_X
-  FH_SET((k_mid<-1, NF>));
-  FH_SET((k_mid<1, NF>));
-  FH_SET((k_mid_frow<-1, NF>));
-  FH_SET((k_mid_frow<1, NF>));
-  FH_SET((k_outer_frow<NF>));
-#define FH_O(SM, D) FH_SET((k_outer<OUTER_PROJECT, SM, D, NF>)); FH_SET((k_outer<OUTER_FWD, SM, D, NF>)); FH_SET((k_outer<OUTER_INV, SM, D, NF>));
-  if (g.small) {
-    if (g.ndim == 3) { FH_O(1, 3) } else { FH_O(1, 2) }
-  } else {
-    if (g.ndim == 3) { FH_O(0, 3) } else { FH_O(0, 2) }
-  }
-#undef FH_O
-#undef FH_SET
+hipError_t outer_cg_limits(const Geom& g, size_t bytes) {
+  return g.small ? outer_cg_limits<NF, 1>(bytes) : outer_cg_limits<NF, 0>(bytes);
+}
+template <int NF, int SMALL, int NDIM>
+hipError_t outer_limits(size_t bytes) {
+  hipError_t e = raise_limit(k_outer<OUTER_PROJECT, SMALL, NDIM, NF>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_outer<OUTER_FWD, SMALL, NDIM, NF>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_outer<OUTER_INV, SMALL, NDIM, NF>, bytes);
   return e;
+}
+template <int NF>
+hipError_t outer_limits(const Geom& g, size_t bytes) {
+  hipError_t e = raise_limit(k_outer_frow<NF>, bytes);
+  if (e != hipSuccess) return e;
+  if (g.small) return g.ndim == 3 ? outer_limits<NF, 1, 3>(bytes) : outer_limits<NF, 1, 2>(bytes);
+  return g.ndim == 3 ? outer_limits<NF, 0, 3>(bytes) : outer_limits<NF, 0, 2>(bytes);
+}
+template <int NF>
+hipError_t mid_limits(size_t bytes) {
+  hipError_t e = raise_limit(k_mid<-1, NF>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_mid<1, NF>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_mid_frow<-1, NF>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_mid_frow<1, NF>, bytes);
+  return e;
+}
+template <int NF, int C>
+hipError_t xinv_limits(size_t bytes) {
+  hipError_t e = raise_limit(k_xinv<CONS_IDENT, C, NF>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_xinv<CONS_RHS, C, NF>, bytes);
+  if (e == hipSuccess) e = raise_limit(k_xinv<CONS_CGUPD, C, NF>, bytes);
+  return e;
+}
+template <int NF>
+hipError_t xinv_limits(const Geom& g, size_t bytes) {
+  switch (g.c) {
+    case 3: return xinv_limits<NF, 3>(bytes);
+    case 4: return xinv_limits<NF, 4>(bytes);
+    case 6: return xinv_limits<NF, 6>(bytes);
+    case 9: return xinv_limits<NF, 9>(bytes);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace fh

@@ -1,5 +1,5 @@
-// The forward x pass of one constitutive law, for every FFT variant.  The forward x pass holds the
-// law's arithmetic and every producer, so each law is a translation unit of its own (they compile
+// The x passes of one constitutive law, for every FFT variant.  They hold the law's arithmetic and
+// every producer, so each law is a translation unit of its own (they compile
 // beside one another); a unit defines FH_XPASS (its function's name) and FH_XPASS_LAWS(X), a list
 // X(matcode, MAT, NDIM).
 #include "pass_kernels.h"
@@ -10,6 +10,13 @@ namespace {
 
 template <int MAT, int NDIM, int NF>
 hipError_t xfwd_one(int prod, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s) {
+  if constexpr (NDIM == 3) {
+    if (prod == PROD_XOP || prod == PROD_XOP_STORED) {
+      if (prod == PROD_XOP) hipLaunchKernelGGL((k_xop<0, MAT, 3, NF>), grid, dim3(kThreads), sm, s, a);
+      else hipLaunchKernelGGL((k_xop<1, MAT, 3, NF>), grid, dim3(kThreads), sm, s, a);
+      return hipGetLastError();
+    }
+  }
   switch (prod) {
     case PROD_IDENT: hipLaunchKernelGGL((k_xfwd<PROD_IDENT, MAT, NDIM, NF>), grid, dim3(kThreads), sm, s, a); break;
     case PROD_STRESS: hipLaunchKernelGGL((k_xfwd<PROD_STRESS, MAT, NDIM, NF>), grid, dim3(kThreads), sm, s, a); break;
@@ -24,10 +31,12 @@ hipError_t xfwd_one(int prod, const XFwdArgs& a, dim3 grid, size_t sm, hipStream
   return hipGetLastError();
 }
 
-// 3D axes of a length with its own CG-loop kernel
+// 3D axes of a length with its own CG-loop kernels
 template <int MAT, int NF>
-hipError_t xfwd_fixed(const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s) {
-  hipLaunchKernelGGL((k_xfwd<PROD_CGOP, MAT, 3, NF>), grid, dim3(kThreads), sm, s, a);
+hipError_t xfwd_fixed(int prod, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s) {
+  if (prod == PROD_XOP) hipLaunchKernelGGL((k_xop<0, MAT, 3, NF>), grid, dim3(kThreads), sm, s, a);
+  else if (prod == PROD_CGOP) hipLaunchKernelGGL((k_xfwd<PROD_CGOP, MAT, 3, NF>), grid, dim3(kThreads), sm, s, a);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -40,13 +49,12 @@ hipError_t xfwd_nf(int nf, int prod, const XFwdArgs& a, dim3 grid, size_t sm, hi
     default: break;
   }
   if constexpr (NDIM == 3) {
-    if (prod != PROD_CGOP) return hipErrorInvalidValue;
     switch (nf) {
-      case 128: return xfwd_fixed<MAT, 128>(a, grid, sm, s);
-      case kStaged + 96: return xfwd_fixed<MAT, kStaged + 96>(a, grid, sm, s);
-      case kStaged + 64: return xfwd_fixed<MAT, kStaged + 64>(a, grid, sm, s);
-      case kStaged + 48: return xfwd_fixed<MAT, kStaged + 48>(a, grid, sm, s);
-      case kStaged + 32: return xfwd_fixed<MAT, kStaged + 32>(a, grid, sm, s);
+      case 128: return xfwd_fixed<MAT, 128>(prod, a, grid, sm, s);
+      case kStaged + 96: return xfwd_fixed<MAT, kStaged + 96>(prod, a, grid, sm, s);
+      case kStaged + 64: return xfwd_fixed<MAT, kStaged + 64>(prod, a, grid, sm, s);
+      case kStaged + 48: return xfwd_fixed<MAT, kStaged + 48>(prod, a, grid, sm, s);
+      case kStaged + 32: return xfwd_fixed<MAT, kStaged + 32>(prod, a, grid, sm, s);
       default: break;
     }
   }
@@ -63,6 +71,11 @@ hipError_t limits_one(size_t bytes) {
                          reinterpret_cast<const void*>(k_xfwd<PROD_CGOP_STORED, MAT, NDIM, NF>),
                          reinterpret_cast<const void*>(k_xfwd<PROD_ADJ, MAT, NDIM, NF>)})
     if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if constexpr (NDIM == 3) {
+    for (const void* fn : {reinterpret_cast<const void*>(k_xop<0, MAT, 3, NF>),
+                           reinterpret_cast<const void*>(k_xop<1, MAT, 3, NF>)})
+      if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  }
   return e;
 }
 
@@ -76,7 +89,12 @@ hipError_t limits_all(size_t bytes) {
                            reinterpret_cast<const void*>(k_xfwd<PROD_CGOP, MAT, 3, kStaged + 96>),
                            reinterpret_cast<const void*>(k_xfwd<PROD_CGOP, MAT, 3, kStaged + 64>),
                            reinterpret_cast<const void*>(k_xfwd<PROD_CGOP, MAT, 3, kStaged + 48>),
-                           reinterpret_cast<const void*>(k_xfwd<PROD_CGOP, MAT, 3, kStaged + 32>)})
+                           reinterpret_cast<const void*>(k_xfwd<PROD_CGOP, MAT, 3, kStaged + 32>),
+                           reinterpret_cast<const void*>(k_xop<0, MAT, 3, 128>),
+                           reinterpret_cast<const void*>(k_xop<0, MAT, 3, kStaged + 96>),
+                           reinterpret_cast<const void*>(k_xop<0, MAT, 3, kStaged + 64>),
+                           reinterpret_cast<const void*>(k_xop<0, MAT, 3, kStaged + 48>),
+                           reinterpret_cast<const void*>(k_xop<0, MAT, 3, kStaged + 32>)})
       if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   }
   return e;

@@ -1,0 +1,44 @@
+"""The CG on displacements (3D, tolerances from 1e-11 on) against the CG on strain fields (below).
+
+The same problem just above and just below the tolerance where the form changes, over odd and even
+grids (mirror planes with and without a Nyquist frequency), every FFT variant of its passes (generic
+radix, dense DFT, chirp-z, the lengths with kernels of their own) and both ways of applying the
+tangent.  Either solve stops at a residual of 1e-11 of its right-hand side, which bounds its error by
+the conditioning, at most the contrast 5, times that: the fluctuations and tangents of the two differ
+by at most 2 x 5 x 1e-11 = 1e-10.
+"""
+
+import numpy as np
+import pytest
+
+from paper_2408_03804_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-10
+SHAPES = [(5, 7, 6), (6, 4, 5), (8, 1, 9), (16, 20, 12), (17, 33, 18), (4, 6, 257), (257, 3, 4), (32, 48, 32), (64, 8, 96),
+          (128, 128, 4), (4, 6, 128)]
+
+
+def run(shape, kin, mat, macro, tol, k_mode):
+    from paper_2408_03804_amd.binding import FFTHomog
+    h = FFTHomog(shape, kin, mat, 2, tol_cg=tol, tol_newton=1e-10, tangent=True, k_mode=k_mode)
+    h.set_material(workloads.random_phases(shape, 2, 3), [[2.0, 1.0], [10.0, 5.0]])
+    S, _, st = h.solve(macro, 1)
+    C, _ = h.tangent()
+    return h.get_field(0).cpu().numpy(), S, C, st
+
+
+@pytest.mark.parametrize("k_mode", [0, 1])
+@pytest.mark.parametrize("kin,mat,macro", [("small", "linear_elastic", [1e-2, 0, 0, 0, 5e-3, 0]),
+                                           ("finite", "neo_hookean", [1.02, 0.01, 0, 0, 0.99, 0.02, 0.01, 0, 1.0])])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_both_forms_of_the_cg_agree(shape, kin, mat, macro, k_mode):
+    disp = run(shape, kin, mat, np.array(macro, float), 1e-11, k_mode)
+    strain = run(shape, kin, mat, np.array(macro, float), 0.99e-11, k_mode)
+    assert disp[3]["status"] == strain[3]["status"] == "ok"
+    axes = tuple(range(1, disp[0].ndim))
+    mean = strain[0].mean(axis=axes, keepdims=True)
+    assert np.linalg.norm(disp[0] - strain[0]) < TOL * np.linalg.norm(strain[0] - mean)
+    assert np.abs(disp[1] - strain[1]).max() < TOL * np.abs(strain[1]).max()
+    assert np.abs(disp[2] - strain[2]).max() < TOL * np.abs(strain[2]).max()
