@@ -3,11 +3,12 @@
 // Every layer is a bf16 x bf16 -> fp32 GEMM on gfx950 MFMA 16x16x32 tiles:
 //   conv forward      pre[m][co]   = col[m][k] . W[co][k]            (col = periodic stride-2 im2col)
 //   conv weight grad  dW[co][k]    = sum_m dpre[m][co] col[m][k]      (split over m, fixed-order sum)
-//   conv input grad   dcol[m][k]   = sum_co dpre[m][co] W[co][k], then a gather back to the voxels
-// col is never stored for blocks 2-4: their GEMM tile loaders gather it from the previous
-// block's activations (implicit GEMM); block 1 (one input channel, the u8 phase map) expands it.
+//   conv input grad   dcol[m][k]   = sum_co dpre[m][co] W[co][k], gathered back to the voxels
+// col and dcol are never stored where the channels are multiples of 8: the tile loaders gather their
+// operands from the previous block's activations, the phase map or dpre (implicit GEMM).  Bias and gelu
+// (their derivative in the input gradient) are applied to the accumulators.
 //   dense layers      the same three products with m = sample
-// around small element-wise kernels (bias + gelu, pooling, loss, Adam).  All sums that
+// around small element-wise kernels (pooling, loss, Adam).  All sums that
 // cross blocks go through partial buffers reduced in a fixed order, so a training step is
 // bitwise reproducible.
 #include <hip/hip_runtime.h>
@@ -15,6 +16,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "fft_homog.h"
@@ -27,7 +29,7 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kT = 256;
-constexpr int BM = 64, BN = 64, BK = 32, LDT = BK + 8;  // GEMM tile; LDS row pitch in bf16
+constexpr int BM = 64, BN = 64, BK = 128;  // GEMM tile
 constexpr int kMaxSplits = 1024;
 constexpr int kColRows = 256;  // rows per block of the bias-gradient column sums
 
@@ -46,6 +48,18 @@ __device__ inline float gelu_grad(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * expf(-0.5f * x * x);
 }
 
+// quotient by d of r < 2^31 (magic = ceil(2^(31 + s) / d), 2^s >= d: exact over that range)
+struct Div {
+  uint32_t d, magic, s;
+};
+Div make_div(int d) {
+  Div f{(uint32_t)d, 0, 0};
+  while ((1u << f.s) < f.d) ++f.s;
+  f.magic = (uint32_t)(((1ull << (31 + f.s)) + f.d - 1) / f.d);
+  return f;
+}
+__device__ inline uint32_t quot(uint32_t r, const Div& f) { return __umulhi(r << 1, f.magic) >> f.s; }
+
 // ---------------------------------------------------------------------------
 // GEMM: C[z][m][n] = sum_{k in split z} A(m,k) B(n,k)
 // ---------------------------------------------------------------------------
@@ -55,8 +69,14 @@ __device__ inline float gelu_grad(float x) {
 // zero for k >= 27 Ci.  Ci % 8 == 0, so 8 consecutive k share a tap (one 16-byte load).
 struct ConvOperand {
   const bf16* src;  // [b][z][y][x][Ci] activations of the previous block
-  int n, m, Ci;
+  int n, Ci;
+  Div m, ci;
 };
+
+// operands of k_gemm: from memory, contiguous along k or along rows; the im2col operand, k along its
+// columns (forward) or along its rows (weight gradient); block 1's 27 taps as bits, k along rows
+enum Operand { OP_K, OP_ROW, OP_COL, OP_COLT, OP_BITS };
+constexpr bool along_k(int op) { return op == OP_K || op == OP_COL; }
 
 struct GemmArgs {
   int M, N, K, kchunk;
@@ -64,8 +84,11 @@ struct GemmArgs {
   long long sam, sak;
   const bf16* B;
   long long sbn, sbk;
-  float* C;
-  ConvOperand cv;  // the implicit operand (A for CONV = 1, B for CONV = 2)
+  float* C;               // product, or with bias: product + bias (nullable)
+  const float* bias;
+  bf16* act;              // bf16(gelu(C)) (nullable)
+  ConvOperand cv;         // the implicit operand (A for OP_COL, B for OP_COLT)
+  const uint8_t* bits;    // OP_BITS: 4 bytes per output row
 };
 
 // periodic input coordinate of output coordinate o and tap component t (0..2)
@@ -76,171 +99,484 @@ __device__ inline int tap_coord(int o, int t, int n) {
   return i;
 }
 
-// The 8 col entries (row, k..k+7) of the implicit operand (zero past 27 Ci); (b, oz, oy, ox) is row.
-__device__ inline uint4 conv_gather(const ConvOperand& c, long long b, int oz, int oy, int ox, int k) {
-  const int tap = k / c.Ci;
-  if (tap >= 27) return make_uint4(0u, 0u, 0u, 0u);
-  const int ci = k - tap * c.Ci;
-  const int tz = tap / 9, ty = (tap / 3) % 3, tx = tap % 3;
-  const long long vox = ((b * c.n + tap_coord(oz, tz, c.n)) * c.n + tap_coord(oy, ty, c.n)) * c.n + tap_coord(ox, tx, c.n);
-  return *reinterpret_cast<const uint4*>(c.src + vox * c.Ci + ci);
-}
-
 // output row -> (sample, oz, oy, ox); rows are below 2^31 (max_batch m^3 outputs per block)
-__device__ inline void conv_row(const ConvOperand& c, int row, long long* b, int* oz, int* oy, int* ox) {
-  const unsigned m = (unsigned)c.m;
-  unsigned r = (unsigned)row;
-  unsigned q = r / m;
-  *ox = (int)(r - q * m);
+struct Row {
+  uint32_t b;
+  int z, y, x;
+};
+__device__ inline Row row_of(uint32_t r, const Div& m) {
+  Row w;
+  uint32_t q = quot(r, m);
+  w.x = (int)(r - q * m.d);
   r = q;
-  q = r / m;
-  *oy = (int)(r - q * m);
+  q = quot(r, m);
+  w.y = (int)(r - q * m.d);
   r = q;
-  q = r / m;
-  *oz = (int)(r - q * m);
-  *b = q;
+  w.b = quot(r, m);
+  w.z = (int)(r - w.b * m.d);
+  return w;
+}
+// Addresses of the im2col operand without a wrap per coordinate: an output's centre tap, and a tap's offset
+// from it.  Only tap component 0 of output coordinate 0 leaves the cell, by -1: it gets the axis length
+// back (both masks set).  The divisions and wraps of every entry were most of the loaders' instructions.
+struct OutputRef {
+  const bf16* p;
+  int fz, fy, fx;  // -1 where the output coordinate is 0
+};
+__device__ inline OutputRef output_ref(const ConvOperand& c, uint32_t row) {
+  const Row w = row_of(row, c.m);
+  OutputRef r;
+  r.p = c.src + (((w.b * (long long)c.n + 2 * w.z) * c.n + 2 * w.y) * c.n + 2 * w.x) * c.Ci;
+  r.fz = w.z == 0 ? -1 : 0;
+  r.fy = w.y == 0 ? -1 : 0;
+  r.fx = w.x == 0 ? -1 : 0;
+  return r;
+}
+struct TapOffset {
+  int off, wz, wy, wx;  // a cell's activations are at most 2^28 entries
+};
+__device__ inline TapOffset tap_offset(const ConvOperand& c, int tap, int ci) {
+  const int tz = tap / 9, ty = (tap / 3) % 3, tx = tap % 3;
+  TapOffset t;
+  t.off = (((tz - 1) * c.n + ty - 1) * c.n + tx - 1) * c.Ci + ci;
+  t.wx = tx == 0 ? c.n * c.Ci : 0;
+  t.wy = ty == 0 ? c.n * c.n * c.Ci : 0;
+  t.wz = tz == 0 ? c.n * c.n * c.n * c.Ci : 0;
+  return t;
+}
+__device__ inline uint4 conv_gather(const OutputRef& r, const TapOffset& t) {
+  return *reinterpret_cast<const uint4*>(r.p + (t.off + (r.fz & t.wz) + (r.fy & t.wy) + (r.fx & t.wx)));
 }
 
-// Stage a 64 x 32 (rows x k) operand tile into LDS, zero outside [0,nrows) x [k0,kend).
-// KC: the operand is contiguous along k (else along rows).
+// Tiles of 64 rows x BK in LDS, in 16-byte groups of 8 k: group g of row r at g ^ (r ^ r / 8) mod 8.
+// So neither the reads of the MFMA operands (16 rows at one g), nor the 16-byte stores along k, nor
+// the 4-byte stores of an operand that is contiguous along rows (8 rows of 8, two k each) meet in a bank.
+__device__ inline int tile_at(int r, int g) { return r * BK + ((g ^ ((r ^ (r >> 3)) & 7)) << 3); }
+
+// This thread's p-th (of 4) 8 entries of a tile: along k, row t / 16 + 16 p at group t mod 16; along
+// rows, 8 (t mod 8) .. + 7 at k = 2 (t / 8 + 32 (p / 2)) + p mod 2 (so that it holds pairs of k).
+__device__ inline int chunk_row(bool kc, int p) { return kc ? ((int)threadIdx.x >> 4) + 16 * p : ((int)threadIdx.x & 7) * 8; }
+__device__ inline int chunk_k(bool kc, int p) {
+  return kc ? ((int)threadIdx.x & 15) * 8 : 2 * (((int)threadIdx.x >> 3) + 32 * (p >> 1)) + (p & 1);
+}
+
+// Four chunks of an operand in memory, zero outside [0, nrows) x [.., kend).  VEC: every chunk inside is
+// 16 aligned bytes.  Loads are then unconditional, from a clamped address, and chunks outside are cleared
+// when they are stored (ok): a load under a condition is waited for where its branch ends, not where its
+// value is used, which left nothing in flight during the products.
+struct Chunks {
+  uint4 v[4];
+  bool ok[4];
+};
+template <bool KC, bool VEC>
+__device__ inline void fetch_tile(Chunks& f, const bf16* P, long long s_row, long long s_k, int row0, int nrows, int k0,
+                                  int kend) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int row = row0 + chunk_row(KC, p);
+    const int k = k0 + chunk_k(KC, p);
+    f.ok[p] = row < nrows && k < kend;
+    if constexpr (VEC) {
+      const int rc = min(row, KC ? nrows - 1 : nrows - 8), kc = min(k, KC ? kend - 8 : kend - 1);
+      f.v[p] = *reinterpret_cast<const uint4*>(P + (long long)rc * s_row + (long long)kc * s_k);
+    } else {
+      f.v[p] = make_uint4(0u, 0u, 0u, 0u);
+      if (!f.ok[p]) continue;
+      const bf16* src = P + (long long)row * s_row + (long long)k * s_k;
+      const int left = KC ? kend - k : nrows - row;  // entries of the 8 inside
+      uint64_t lo = 0, hi = 0;
+#pragma unroll 1
+      for (int i = 0; i < min(left, 8); ++i) {
+        const uint64_t e = (uint64_t)src[i] << (16 * (i & 3));
+        if (i < 4) lo |= e;
+        else hi |= e;
+      }
+      f.v[p] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    }
+  }
+}
+
 template <bool KC>
-__device__ inline void load_tile(bf16 (*T)[LDT], const bf16* P, long long s_row, long long s_k, int row0, int nrows,
-                                 int k0, int kend) {
-  const int t = threadIdx.x;
-  bf16 v[8];
-  if (KC) {
-    const int r = t >> 2;
-    const int kk = (t & 3) * 8;
-    const int row = row0 + r;
-    const int k = k0 + kk;
-    const bf16* src = P + (long long)row * s_row + (long long)k * s_k;
-    if (row < nrows && k + 8 <= kend && ((reinterpret_cast<uintptr_t>(src) & 15u) == 0)) {
-      const uint4 q = *reinterpret_cast<const uint4*>(src);
-      memcpy(v, &q, 16);
-    } else {
+__device__ inline void store_tile(bf16* T, const Chunks& f) {
+  uint4 v[4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = (row < nrows && k + i < kend) ? P[(long long)row * s_row + (long long)(k + i) * s_k] : 0;
-    }
-    uint4 q;
-    memcpy(&q, v, 16);
-    *reinterpret_cast<uint4*>(&T[r][kk]) = q;
+  for (int p = 0; p < 4; ++p) v[p] = f.ok[p] ? f.v[p] : make_uint4(0u, 0u, 0u, 0u);
+  if constexpr (KC) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      *reinterpret_cast<uint4*>(T + tile_at(chunk_row(true, p), (int)threadIdx.x & 15)) = v[p];
   } else {
-    const int kk = t >> 3;
-    const int rr = (t & 7) * 8;
-    const int k = k0 + kk;
-    const int row = row0 + rr;
-    const bf16* src = P + (long long)row * s_row + (long long)k * s_k;
-    if (k < kend && row + 8 <= nrows && ((reinterpret_cast<uintptr_t>(src) & 15u) == 0)) {
-      const uint4 q = *reinterpret_cast<const uint4*>(src);
-      memcpy(v, &q, 16);
-    } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = (k < kend && row + i < nrows) ? P[(long long)(row + i) * s_row + (long long)k * s_k] : 0;
+    for (int p = 0; p < 4; p += 2) {
+      const int r = chunk_row(false, p), k = chunk_k(false, p);
+      const uint32_t a[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
+      const uint32_t b[4] = {v[p + 1].x, v[p + 1].y, v[p + 1].z, v[p + 1].w};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t lo = (i & 1) ? a[i >> 1] >> 16 : a[i >> 1] & 0xffffu;
+        const uint32_t hi = (i & 1) ? b[i >> 1] & 0xffff0000u : b[i >> 1] << 16;
+        *reinterpret_cast<uint32_t*>(T + tile_at(r + i, k >> 3) + (k & 7)) = lo | hi;
+      }
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) T[rr + i][kk] = v[i];
   }
 }
 
 // 256 threads = 4 waves in a 2 x 2 arrangement, each wave a 32 x 32 block of 2 x 2 MFMA tiles.
 // gfx950 MFMA 16x16x32 bf16 (v_mfma_f32_16x16x32_bf16, one instruction per 32-deep k step of a tile):
-// lane l holds rows/cols (l mod 16) at k = 8 (l / 16) + 0..7 (one 16-byte LDS read per operand);
-// the accumulator holds column (l mod 16), rows 4 (l / 16) + 0..3.
-// CONV = 1: A is the implicit im2col operand g.cv (rows = outputs, contiguous along k);
-// CONV = 2: B is (B rows = col k, GEMM k = outputs).  The other operand is read from memory.
-template <bool AK, bool BK_, int CONV = 0>
-__global__ void __launch_bounds__(kT) k_gemm(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) bf16 As[BM][LDT];
-  __shared__ __attribute__((aligned(16))) bf16 Bs[BN][LDT];
+// lane l holds rows/cols (l mod 16) at k = 8 (l / 16) + 0..7 (one 16-byte LDS read per operand).  B is
+// the first operand, so the accumulator of lane l holds C row (l mod 16), columns 4 (l / 16) + 0..3:
+// 16-byte stores.
+struct WaveTile {
+  int m, n, lr, lk;  // C row of acc[i]: m + 16 i + lr, columns of acc[.][j]: n + 16 j + lk + 0..3
+  // narrow: the four waves hold 16 rows x 32 columns each, one below the other
+  __device__ inline explicit WaveTile(bool narrow = false) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    m = narrow ? w * 16 : (w >> 1) * 32;
+    n = narrow ? 0 : (w & 1) * 32;
+    lr = lane & 15;
+    lk = 4 * (lane >> 4);
+  }
+};
+template <int I>
+__device__ inline void mfma_step(v4f (&acc)[I][2], const bf16* As, const bf16* Bs, const WaveTile& w, int ks) {
+  v8bf a[I], b[2];
+#pragma unroll
+  for (int i = 0; i < I; ++i) a[i] = *reinterpret_cast<const v8bf*>(As + tile_at(w.m + 16 * i + w.lr, 4 * ks + (w.lk >> 2)));
+#pragma unroll
+  for (int i = 0; i < 2; ++i) b[i] = *reinterpret_cast<const v8bf*>(Bs + tile_at(w.n + 16 * i + w.lr, 4 * ks + (w.lk >> 2)));
+#pragma unroll
+  for (int i = 0; i < I; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+}
+__device__ inline void mfma_tile(v4f (&acc)[2][2], const bf16* As, const bf16* Bs, const WaveTile& w, int depth) {
+#pragma unroll
+  for (int ks = 0; ks < BK / 32; ++ks)
+    if (32 * ks < depth) mfma_step(acc, As, Bs, w, ks);
+}
+
+// Four consecutive columns of a row of the product: x + bias into C and bf16(gelu) into act (either may
+// be null), or x into C if there is no bias.  wide: rows of C and act are 16- and 8-byte aligned.
+__device__ inline void store_row4(v4f x, int col, int N, bool wide, const float* bias, float* C, bf16* act) {
+  if (bias) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (col + e < N) x[e] += bias[col + e];
+  }
+  if (wide && col + 3 < N) {
+    if (C) *reinterpret_cast<v4f*>(C + col) = x;
+    if (act) {
+      const uint32_t lo = (uint32_t)to_bf16(gelu(x[0])) | ((uint32_t)to_bf16(gelu(x[1])) << 16);
+      const uint32_t hi = (uint32_t)to_bf16(gelu(x[2])) | ((uint32_t)to_bf16(gelu(x[3])) << 16);
+      *reinterpret_cast<uint2*>(act + col) = make_uint2(lo, hi);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (col + e < N) {
+        if (C) C[col + e] = x[e];
+        if (act) act[col + e] = to_bf16(gelu(x[e]));
+      }
+  }
+}
+
+// Bound by the latency of the operand loads and the instructions that form their addresses (the products
+// of a training step are 50 GFLOP, 40 us at the card's rate): a block keeps the next BK of both operands
+// on their way to registers while it multiplies this one (two ahead gained nothing).  With one 32-deep
+// step at a time the conv products of 256 cells of 32^3 took, in mean, 67 us (forward, blocks 2-4) and
+// 141 us (weight gradient), now 39 and 51 us; block 1's weight gradient 78, now 50 us.
+template <int AOP, int BOP, bool VEC>
+__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(3))) k_gemm(GemmArgs g) {
+  __shared__ __attribute__((aligned(16))) bf16 As[BM * BK];
+  __shared__ __attribute__((aligned(16))) bf16 Bs[BN * BK];
   const int m0 = blockIdx.x * BM;
   const int n0 = blockIdx.y * BN;
   const int kbeg = blockIdx.z * g.kchunk;
   const int kend = min(g.K, kbeg + g.kchunk);
-  const int lane = threadIdx.x & 63;
-  const int w = threadIdx.x >> 6;
-  const int wm = (w >> 1) * 32;
-  const int wn = (w & 1) * 32;
-  const int lr = lane & 15;
-  const int lk = 4 * (lane >> 4);   // accumulator rows
-  const int lk8 = 8 * (lane >> 4);  // operand k offset
+  const WaveTile w;
   v4f acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  // CONV = 1: this thread's A row of every k tile (row r = t / 4, k offset 8 (t mod 4))
-  long long cb = 0;
-  int coz = 0, coy = 0, cox = 0;
-  const int crow = m0 + (threadIdx.x >> 2);
-  if (CONV == 1 && crow < g.M) conv_row(g.cv, crow, &cb, &coz, &coy, &cox);
+  // OP_COL: the outputs of this thread's rows.  OP_COLT: its tap and channel.
+  OutputRef arow[4] = {};
+  if constexpr (AOP == OP_COL) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) arow[p] = output_ref(g.cv, (uint32_t)min(m0 + chunk_row(true, p), g.M - 1));
+  }
+  const int kcol = n0 + chunk_row(false, 0);
+  int btap = 0;
+  TapOffset boff = {};
+  if constexpr (BOP == OP_COLT) {
+    btap = (int)quot((uint32_t)kcol, g.cv.ci);
+    boff = tap_offset(g.cv, min(btap, 26), btap < 27 ? kcol - btap * g.cv.Ci : 0);
+  }
+  Chunks fa, fb;
+  auto fetch = [&](int k0) {
+    if constexpr (AOP == OP_COL) {
+      const int k = k0 + chunk_k(true, 0);
+      const int tap = (int)quot((uint32_t)k, g.cv.ci);
+      const TapOffset t = tap_offset(g.cv, min(tap, 26), tap < 27 ? k - tap * g.cv.Ci : 0);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        fa.ok[p] = m0 + chunk_row(true, p) < g.M && k < kend && tap < 27;
+        fa.v[p] = conv_gather(arow[p], t);
+      }
+    } else {
+      fetch_tile<AOP == OP_K, VEC>(fa, g.A, g.sam, g.sak, m0, g.M, k0, kend);
+    }
+    if constexpr (BOP == OP_COLT || BOP == OP_BITS) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int row = k0 + chunk_k(false, p), rc = min(row, kend - 1);
+        fb.ok[p] = row < kend && kcol < g.N;
+        if constexpr (BOP == OP_COLT) {
+          fb.ok[p] = fb.ok[p] && btap < 27;
+          fb.v[p] = conv_gather(output_ref(g.cv, (uint32_t)rc), boff);
+        } else {
+          fb.v[p].x = g.bits[4 * (long long)rc + (min(kcol, g.N - 8) >> 3)];  // expanded when it is stored
+        }
+      }
+    } else {
+      fetch_tile<BOP == OP_K, VEC>(fb, g.B, g.sbn, g.sbk, n0, g.N, k0, kend);
+    }
+  };
+  auto put = [&] {
+    if constexpr (BOP == OP_BITS) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const uint32_t t = fb.v[p].x;
+        auto two = [&](int i) { return ((t >> i) & 1u) * 0x3f80u | ((t >> (i + 1)) & 1u) * 0x3f800000u; };
+        fb.v[p] = make_uint4(two(0), two(2), two(4), two(6));
+      }
+    }
+    store_tile<along_k(AOP)>(As, fa);
+    store_tile<along_k(BOP)>(Bs, fb);
+  };
+  fetch(kbeg);
   for (int k0 = kbeg; k0 < kend; k0 += BK) {
-    if constexpr (CONV == 1) {
-      const int kk = (threadIdx.x & 3) * 8;
-      uint4 q = make_uint4(0u, 0u, 0u, 0u);
-      if (crow < g.M && k0 + kk < kend) q = conv_gather(g.cv, cb, coz, coy, cox, k0 + kk);
-      *reinterpret_cast<uint4*>(&As[threadIdx.x >> 2][kk]) = q;
-    } else {
-      load_tile<AK>(As, g.A, g.sam, g.sak, m0, g.M, k0, kend);
-    }
-    if constexpr (CONV == 2) {
-      // GEMM k = output row k0 + t / 8, B rows (col k) n0 + 8 (t mod 8) .. + 7, stored transposed
-      const int kk = threadIdx.x >> 3;
-      const int rr = (threadIdx.x & 7) * 8;
-      uint4 q = make_uint4(0u, 0u, 0u, 0u);
-      if (k0 + kk < kend && n0 + rr < g.N) {
-        long long b;
-        int oz, oy, ox;
-        conv_row(g.cv, k0 + kk, &b, &oz, &oy, &ox);
-        q = conv_gather(g.cv, b, oz, oy, ox, n0 + rr);
-      }
-      bf16 v[8];
-      memcpy(v, &q, 16);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) Bs[rr + i][kk] = v[i];
-    } else {
-      load_tile<BK_>(Bs, g.B, g.sbn, g.sbk, n0, g.N, k0, kend);
-    }
+    put();
     __syncthreads();
-    static_assert(BK == 32, "one 16x16x32 MFMA per k tile");
-    {
-      v8bf a[2], b[2];
+    if (k0 + BK < kend) fetch(k0 + BK);
+    mfma_tile(acc, As, Bs, w, kend - k0);
+    __syncthreads();
+  }
+  float* C = g.C ? g.C + (long long)blockIdx.z * g.M * g.N : nullptr;
+  const bool wide = (g.N & 3) == 0 && ((reinterpret_cast<uintptr_t>(C) & 15u) == 0);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        a[i] = *reinterpret_cast<const v8bf*>(&As[wm + 16 * i + lr][lk8]);
-        b[i] = *reinterpret_cast<const v8bf*>(&Bs[wn + 16 * i + lr][lk8]);
+  for (int i = 0; i < 2; ++i) {
+    const int row = m0 + w.m + 16 * i + w.lr;
+    if (row >= g.M) continue;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      store_row4(acc[i][j], n0 + w.n + 16 * j + w.lk, g.N, wide, g.bias, C ? C + (long long)row * g.N : nullptr,
+                 g.act ? g.act + (long long)row * g.N : nullptr);
+  }
+}
+
+// First conv block (27 taps of the u8 phase map, K = 32): pre = col W + bias, act = bf16(gelu(pre)).
+// Bound by those stores, 134 + 67 MB for 256 cells of 32^3 with 32 channels.  A wave builds the MFMA
+// operands of 64 output rows from the phase bytes (lane l: row l mod 16, taps 8 (l / 16) + 0..7), keeps
+// the taps as bits for the weight gradient (bits nullable), and multiplies without LDS: 90 us.  The
+// expanded operand alone took 36 us and a bias and gelu pass 106 us, beside the product.  Ids above 1
+// raise *bad.
+__global__ void __launch_bounds__(kT) k_conv_phase(const uint8_t* phase, int M, int n, Div m, const bf16* W, int N,
+                                                   const float* bias, float* pre, bf16* act, uint8_t* bits, int* bad) {
+  const int lane = threadIdx.x & 63, lr = lane & 15, kg = lane >> 4;
+  const int row0 = (blockIdx.x * (kT / 64) + (threadIdx.x >> 6)) * 64;
+  if (row0 >= M) return;
+  v8bf a[4];
+  uint32_t over = 0;
+#pragma unroll
+  for (int it = 0; it < 4; ++it) {
+    const int row = row0 + 16 * it + lr;
+    const Row w = row_of((uint32_t)min(row, M - 1), m);
+    const uint8_t* pb = phase + (long long)w.b * n * n * n;
+    uint32_t t8 = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int tap = min(8 * kg + i, 26);
+      const int tz = tap / 9, ty = (tap / 3) % 3, tx = tap % 3;
+      const uint32_t p = pb[(tap_coord(w.z, tz, n) * n + tap_coord(w.y, ty, n)) * n + tap_coord(w.x, tx, n)];
+      over |= p >> 1;
+      if (8 * kg + i < 27) t8 |= (p ? 1u : 0u) << i;
+    }
+    if (bits && row < M) bits[4 * (long long)row + kg] = (uint8_t)t8;
+    uint32_t e[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) e[i] = ((t8 >> (2 * i)) & 1u) * 0x3f80u | ((t8 >> (2 * i + 1)) & 1u) * 0x3f800000u;
+    memcpy(&a[it], e, 16);
+  }
+  if (over) *bad = 1;
+  const bool wide = (N & 3) == 0;
+  for (int n0 = 0; n0 < N; n0 += 64) {
+    v8bf b[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = *reinterpret_cast<const v8bf*>(W + (long long)min(n0 + 16 * j + lr, N - 1) * 32 + 8 * kg);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int row = row0 + 16 * it + lr;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (n0 + 16 * j >= N) continue;
+        const v4f x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[it], v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        if (row < M)
+          store_row4(x, n0 + 16 * j + 4 * kg, N, wide, bias, pre ? pre + (long long)row * N : nullptr, act + (long long)row * N);
       }
+    }
+  }
+}
+
+// Input gradient of a conv block l > 1, times gelu'(pre of block l - 1), in fp32 (for the bias gradient) and
+// bf16.  For 256 cells of 32^3, blocks 2, 3 and 4: 161 + 46 + 31 us.  (Column sums of the fp32 values made here, without
+// storing them, saved another 40 us, but in another order than k_colsum_partial's: Adam's first steps
+// turn a last-bit change of a gradient near zero into a change of a weight's step.)
+// Voxel i of an axis of length n = 2 m is tap t of output o when 2 o + t - 1 = i (mod n): t = 1 (o = i/2)
+// for even i, t = 0 (o = (i+1)/2 mod m) and t = 2 (o = (i-1)/2) for odd i.  So the voxels of one parity
+// class (blockIdx.z) share their 1, 2, 4 or 8 taps, and their gradient is a product over taps and output
+// channels whose operand rows are those of dpre.  Each tap is summed over the channels by itself and the
+// taps are added in order, as if the product had been formed for all taps and then gathered; that took
+// 165 + 308 us for the same three, mostly for the fp32 products in memory.
+struct DgradArgs {
+  int M, Ci, Co, Kp, n;  // M = B m^3 voxels of a class
+  Div m, co;             // co: of the 32-padded output channels
+  const bf16 *dpre, *W;  // [outputs][Co], [Co][Kp]
+  const float* pre;      // [voxels][Ci]
+  float* d32;
+  bf16* db;
+};
+// NARROW: at most 32 input channels; the waves split the rows only (half of them would have no column).
+template <bool NARROW>
+__global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(3))) k_dgrad(DgradArgs g) {
+  constexpr int I = NARROW ? 1 : 2;
+  __shared__ __attribute__((aligned(16))) bf16 As[BM * BK];
+  __shared__ __attribute__((aligned(16))) bf16 Bs[BN * BK];
+  const int m0 = blockIdx.x * BM;
+  const int n0 = blockIdx.y * BN;
+  const int cls = 7 - blockIdx.z;  // the classes with most taps first
+  const int pz = cls >> 2, py = (cls >> 1) & 1, px = cls & 1;
+  const int m = (int)g.m.d;
+  const WaveTile w(NARROW);
+  v4f sum[I][2], acc[I][2];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < I; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    for (int j = 0; j < 2; ++j) sum[i][j] = acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  // output j of each of this thread's rows, and the way from it to output j + 1 (mod m) along each axis
+  const bf16* arow[4];
+  int dz[4], dy[4], dx[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const Row r = row_of((uint32_t)min(m0 + chunk_row(true, p), g.M - 1), g.m);
+    arow[p] = g.dpre + (((r.b * (long long)m + r.z) * m + r.y) * m + r.x) * g.Co;
+    dz[p] = (r.z + 1 == m ? 1 - m : 1) * m * m * g.Co;
+    dy[p] = (r.y + 1 == m ? 1 - m : 1) * m * g.Co;
+    dx[p] = (r.x + 1 == m ? 1 - m : 1) * g.Co;
+  }
+  // k axis of the product: (tap, 32-padded channel), the taps' x components fastest
+  const int cop = (int)g.co.d;
+  const int K = cop << (pz + py + px);
+  Chunks fa, fb;
+  // tap component of the c-th tap of an axis (c = 0 of an odd voxel is on output j + 1, all others on j)
+  auto tap = [](int par, int c) { return par ? 2 * c : 1; };
+  auto fetch = [&](int k0) {
+    {
+      const int k = k0 + chunk_k(true, 0);
+      const int q = (int)quot((uint32_t)k, g.co), c = k - q * cop;
+      const int cx = q & px, cy = (q >> px) & py, cz = (q >> (px + py)) & pz;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int off = (dz[p] & (cz - pz)) + (dy[p] & (cy - py)) + (dx[p] & (cx - px)) + min(c, g.Co - 8);
+        fa.ok[p] = m0 + chunk_row(true, p) < g.M && k < K && c < g.Co;
+        fa.v[p] = *reinterpret_cast<const uint4*>(arow[p] + off);
+      }
+    }
+    const int ci = n0 + chunk_row(false, 0);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int k = k0 + chunk_k(false, p);
+      const int q = (int)quot((uint32_t)k, g.co), c = k - q * cop;
+      const int cx = q & px, cy = (q >> px) & py, cz = (q >> (px + py)) & pz;
+      const int t = (tap(pz, cz) * 3 + tap(py, cy)) * 3 + tap(px, cx);
+      fb.ok[p] = k < K && c < g.Co && ci < g.Ci;
+      fb.v[p] = *reinterpret_cast<const uint4*>(g.W + (long long)min(c, g.Co - 1) * g.Kp + t * g.Ci + min(ci, g.Ci - 8));
+    }
+  };
+  fetch(0);
+  int left = cop;  // channels of this tap still to be summed
+  for (int k0 = 0; k0 < K; k0 += BK) {
+    store_tile<true>(As, fa);
+    store_tile<false>(Bs, fb);
+    __syncthreads();
+    if (k0 + BK < K) fetch(k0 + BK);
+    const int steps = min(BK, K - k0) / 32;
+    for (int ks = 0; ks < steps; ++ks) {
+      mfma_step(acc, As, Bs, w, ks);
+      left -= 32;
+      if (left == 0) {
+        left = cop;
+#pragma unroll
+        for (int i = 0; i < I; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            sum[i][j] += acc[i][j];
+            acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+          }
+      }
     }
     __syncthreads();
   }
-  float* C = g.C + (long long)blockIdx.z * g.M * g.N;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < I; ++i) {
+    const int row = m0 + w.m + 16 * i + w.lr;
+    if (row >= g.M) continue;
+    const Row r = row_of((uint32_t)row, g.m);
+    const long long vox = ((r.b * (long long)g.n + 2 * r.z + pz) * g.n + 2 * r.y + py) * g.n + 2 * r.x + px;
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j) {
+      const int col = n0 + w.n + 16 * j + w.lk;
+      if (col >= g.Ci) continue;  // Ci is a multiple of 8
+      const v4f pr = *reinterpret_cast<const v4f*>(g.pre + vox * g.Ci + col);
+      v4f o;
+      uint32_t h[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int row = m0 + wm + 16 * i + lk + e;
-        const int col = n0 + wn + 16 * j + lr;
-        if (row < g.M && col < g.N) C[(long long)row * g.N + col] = acc[i][j][e];
+        o[e] = sum[i][j][e] * gelu_grad(pr[e]);
+        h[e] = to_bf16(o[e]);
       }
+      *reinterpret_cast<v4f*>(g.d32 + vox * g.Ci + col) = o;
+      *reinterpret_cast<uint2*>(g.db + vox * g.Ci + col) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+    }
+  }
 }
 
+// k range of each of at most `splits` splits (a multiple of the MFMA's 32), and the splits this makes
+int split_chunk(int K, int splits, int* used) {
+  splits = std::max(1, std::min(splits, kMaxSplits));
+  int chunk = (K + splits - 1) / splits;
+  chunk = (chunk + 31) / 32 * 32;
+  *used = (K + chunk - 1) / chunk;
+  return chunk;
+}
+
+// an operand whose rows of `extent` contiguous entries, `stride` apart, are whole aligned chunks of 8
+bool vector_chunks(const bf16* P, long long stride, int extent) {
+  return extent % 8 == 0 && stride % 8 == 0 && (reinterpret_cast<uintptr_t>(P) & 15u) == 0;
+}
+
+// C (and with bias: act) of operands in memory; *used: the k-splits made
 hipError_t gemm(int M, int N, int K, const bf16* A, long long sam, long long sak, const bf16* B, long long sbn,
-                long long sbk, float* C, int splits, hipStream_t s) {
+                long long sbk, float* C, int splits, hipStream_t s, const float* bias = nullptr, bf16* act = nullptr,
+                int* used = nullptr) {
   if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
-  GemmArgs g;
+  GemmArgs g{};
   g.M = M;
   g.N = N;
   g.K = K;
-  splits = std::max(1, std::min(splits, kMaxSplits));
-  int chunk = (K + splits - 1) / splits;
-  chunk = (chunk + BK - 1) / BK * BK;
-  splits = (K + chunk - 1) / chunk;
-  g.kchunk = chunk;
+  int S;
+  g.kchunk = split_chunk(K, splits, &S);
+  if (used) *used = S;
   g.A = A;
   g.sam = sam;
   g.sak = sak;
@@ -248,19 +584,29 @@ hipError_t gemm(int M, int N, int K, const bf16* A, long long sam, long long sak
   g.sbn = sbn;
   g.sbk = sbk;
   g.C = C;
-  dim3 grid((M + BM - 1) / BM, (N + BN - 1) / BN, splits);
+  g.bias = bias;
+  g.act = act;
+  dim3 grid((M + BM - 1) / BM, (N + BN - 1) / BN, S);
   const bool ak = sak == 1, bk = sbk == 1;
-  if (ak && bk) hipLaunchKernelGGL((k_gemm<true, true>), grid, dim3(kT), 0, s, g);
-  else if (ak) hipLaunchKernelGGL((k_gemm<true, false>), grid, dim3(kT), 0, s, g);
-  else if (bk) hipLaunchKernelGGL((k_gemm<false, true>), grid, dim3(kT), 0, s, g);
-  else hipLaunchKernelGGL((k_gemm<false, false>), grid, dim3(kT), 0, s, g);
+  const bool vec = vector_chunks(A, ak ? sam : sak, ak ? K : M) && vector_chunks(B, bk ? sbn : sbk, bk ? K : N);
+  auto launch = [&](auto v) {
+    constexpr bool VEC = decltype(v)::value;
+    if (ak && bk) hipLaunchKernelGGL((k_gemm<OP_K, OP_K, VEC>), grid, dim3(kT), 0, s, g);
+    else if (ak) hipLaunchKernelGGL((k_gemm<OP_K, OP_ROW, VEC>), grid, dim3(kT), 0, s, g);
+    else if (bk) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_K, VEC>), grid, dim3(kT), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_ROW, VEC>), grid, dim3(kT), 0, s, g);
+  };
+  if (vec) launch(std::true_type{});
+  else launch(std::false_type{});
   return hipGetLastError();
 }
 
-// The two conv products with the implicit im2col operand cv (Kp = 32-padded 27 Ci):
-//   forward      pre[M][N] = col[M][Kp] . W[N][Kp]                    (CONV = 1)
-//   weight grad  dW[z][co][Kp] = sum_{m in split z} dpre[m][co] col[m][Kp]   (CONV = 2; A = dpre, [M][co])
-hipError_t gemm_conv_forward(int M, int N, int Kp, const ConvOperand& cv, const bf16* W, float* C, hipStream_t s) {
+// The two conv products with the implicit im2col operand (Kp = 32-padded 27 Ci):
+//   forward      pre[M][N] = col[M][Kp] . W[N][Kp] + bias, act             (OP_COL)
+//   weight grad  dW[z][co][Kp] = sum_{m in split z} dpre[m][co] col[m][Kp]  (A = dpre, [M][co]; OP_COLT,
+//                or block 1's taps as bits)
+hipError_t gemm_conv_forward(int M, int N, int Kp, const ConvOperand& cv, const bf16* W, const float* bias, float* C,
+                             bf16* act, hipStream_t s) {
   if (M <= 0 || N <= 0 || Kp <= 0) return hipSuccess;
   GemmArgs g{};
   g.M = M;
@@ -271,28 +617,35 @@ hipError_t gemm_conv_forward(int M, int N, int Kp, const ConvOperand& cv, const 
   g.sbn = Kp;
   g.sbk = 1;
   g.C = C;
+  g.bias = bias;
+  g.act = act;
   g.cv = cv;
-  hipLaunchKernelGGL((k_gemm<true, true, 1>), dim3((M + BM - 1) / BM, (N + BN - 1) / BN, 1), dim3(kT), 0, s, g);
+  hipLaunchKernelGGL((k_gemm<OP_COL, OP_K, true>), dim3((M + BM - 1) / BM, (N + BN - 1) / BN, 1), dim3(kT), 0, s, g);
   return hipGetLastError();
 }
-hipError_t gemm_conv_wgrad(int Co, int Kp, int M, const bf16* dpre, const ConvOperand& cv, float* C, int splits,
-                           hipStream_t s) {
+hipError_t gemm_conv_wgrad(int Co, int Kp, int M, const bf16* dpre, const ConvOperand* cv, const uint8_t* bits, float* C,
+                           int splits, hipStream_t s, int* used) {
   if (M <= 0 || Co <= 0 || Kp <= 0) return hipSuccess;
   GemmArgs g{};
   g.M = Co;
   g.N = Kp;
   g.K = M;
-  splits = std::max(1, std::min(splits, kMaxSplits));
-  int chunk = (M + splits - 1) / splits;
-  chunk = (chunk + BK - 1) / BK * BK;
-  splits = (M + chunk - 1) / chunk;
-  g.kchunk = chunk;
+  g.kchunk = split_chunk(M, splits, used);
   g.A = dpre;
   g.sam = 1;
   g.sak = Co;
   g.C = C;
-  g.cv = cv;
-  hipLaunchKernelGGL((k_gemm<false, false, 2>), dim3((Co + BM - 1) / BM, (Kp + BN - 1) / BN, splits), dim3(kT), 0, s, g);
+  g.bits = bits;
+  const dim3 grid((Co + BM - 1) / BM, (Kp + BN - 1) / BN, *used);
+  const bool vec = vector_chunks(dpre, Co, Co);
+  if (cv) {
+    g.cv = *cv;
+    if (vec) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_COLT, true>), grid, dim3(kT), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_COLT, false>), grid, dim3(kT), 0, s, g);
+  } else {
+    if (vec) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_BITS, true>), grid, dim3(kT), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_BITS, false>), grid, dim3(kT), 0, s, g);
+  }
   return hipGetLastError();
 }
 
@@ -333,66 +686,6 @@ __global__ void k_im2col(const bf16* src, int B, int n, int Ci, int Kp, bf16* co
     if (t == 26)
       for (int k = 27 * Ci; k < Kp; ++k) col[row * Kp + k] = 0;
   }
-}
-
-// First block: the input is the u8 phase map (one channel); one thread per output row writes
-// its Kp entries (27 taps, then zeros).  Ids above 1 raise *bad.
-__global__ void k_im2col_phase(const uint8_t* phase, int B, int n, int Kp, bf16* col, int* bad) {
-  const int m = n / 2;
-  const long long rows = (long long)B * m * m * m;
-  for (long long row = blockIdx.x * (long long)blockDim.x + threadIdx.x; row < rows;
-       row += (long long)gridDim.x * blockDim.x) {
-    long long r = row;
-    const int ox = (int)(r % m);
-    r /= m;
-    const int oy = (int)(r % m);
-    r /= m;
-    const int oz = (int)(r % m);
-    const long long b = r / m;
-    const uint8_t* pb = phase + b * n * n * n;
-    bf16* dp = col + row * Kp;
-    // the 27 taps as bits, then 16-byte stores of the bf16 row (Kp is a multiple of 32)
-    uint32_t bits = 0;
-    int t = 0;
-    for (int tz = 0; tz < 3; ++tz) {
-      const int iz = (2 * oz + tz - 1 + n) % n;
-      for (int ty = 0; ty < 3; ++ty) {
-        const int iy = (2 * oy + ty - 1 + n) % n;
-        for (int tx = 0; tx < 3; ++tx, ++t) {
-          const int ix = (2 * ox + tx - 1 + n) % n;
-          const uint8_t p = pb[((long long)iz * n + iy) * n + ix];
-          if (p > 1) *bad = 1;
-          bits |= (p ? 1u : 0u) << t;
-        }
-      }
-    }
-    for (int k0 = 0; k0 < Kp; k0 += 8) {
-      uint32_t wv[4];
-      for (int q = 0; q < 4; ++q) {
-        const int k = k0 + 2 * q;
-        const uint32_t lo = (k < 27 && ((bits >> k) & 1u)) ? 0x3f80u : 0u;
-        const uint32_t hi = (k + 1 < 27 && ((bits >> (k + 1)) & 1u)) ? 0x3f80u : 0u;
-        wv[q] = lo | (hi << 16);
-      }
-      *reinterpret_cast<uint4*>(dp + k0) = make_uint4(wv[0], wv[1], wv[2], wv[3]);
-    }
-  }
-}
-
-// pre[m][n] += bias[n]; act[m][n] = bf16(gelu(pre))   (act may be null).  A block covers
-// kT / N rows (N <= kT) or one row in chunks (N > kT); no per-element division.
-__global__ void k_bias_gelu(float* pre, const float* bias, long long M, int N, bf16* act) {
-  const int rpb = N <= kT ? kT / N : 1;
-  const int c0 = N <= kT ? (int)threadIdx.x % N : (int)threadIdx.x;
-  const int rr = N <= kT ? (int)threadIdx.x / N : 0;
-  if (rr >= rpb) return;
-  for (long long r = (long long)blockIdx.x * rpb + rr; r < M; r += (long long)gridDim.x * rpb)
-    for (int c = c0; c < N; c += (N <= kT ? N : kT)) {
-      const long long e = r * N + c;
-      const float x = pre[e] + bias[c];
-      pre[e] = x;
-      if (act) act[e] = to_bf16(gelu(x));
-    }
 }
 
 // x5[b][:] = [bf16(mean over V voxels of gelu(pre4[b])), bf16(feat[b]), 0 ...]
@@ -460,8 +753,17 @@ __global__ void k_colsum_partial(const float* X, long long M, int C, long long r
     const int c = c0 + tid % cw;
     const int grp = tid / cw;
     float acc = 0.f;
-    if (grp < groups)
-      for (long long r = r0 + grp; r < r1; r += groups) acc += X[r * C + c];
+    // 16 rows on their way at a time, added in order
+    if (grp < groups) {
+      for (long long r = r0 + grp; r < r1; r += 16LL * groups) {
+        float x[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = X[std::min(r + (long long)i * groups, r1 - 1) * C + c];
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (r + (long long)i * groups < r1) acc += x[i];
+      }
+    }
     red[tid] = (grp < groups) ? acc : 0.f;
     __syncthreads();
     if (tid < cw) {
@@ -489,16 +791,43 @@ __global__ void k_colsum_final(const float* partial, int nb, int C, float* dst) 
   if (threadIdx.x == 0) dst[c] = red[0];
 }
 
-// out[n] = sum_s P[s][n] in order (n < N); with `rows`>1, P is [S][rows][N] and out [rows][ldo]
-__global__ void k_sum_splits(const float* P, int S, long long rows, int N, int Nvalid, float* out, int ldo, int accumulate) {
+// out[r][n] = sum over s of P[s][r][n] in order, n < Nvalid, out [rows][ldo].  Few splits: a thread per
+// entry.  Many: 16 entries per block, whose splits are fetched side by side, 256 at a time, and then
+// added one after the other (a thread per entry waited 64 us for the 256 splits of 32 x 27 entries; the
+// other way round, one split of 256 x 3456 entries took 40 us with 16 threads of a block at work).
+constexpr int kFewSplits = 32;
+__global__ void __launch_bounds__(kT) k_sum_few_splits(const float* P, int S, long long rows, int N, int Nvalid, float* out, int ldo) {
   const long long tot = rows * Nvalid;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < tot; e += (long long)gridDim.x * blockDim.x) {
     const long long r = e / Nvalid;
     const int n = (int)(e - r * Nvalid);
     float s = 0.f;
+#pragma unroll 8
     for (int z = 0; z < S; ++z) s += P[((long long)z * rows + r) * N + n];
-    float* dst = out + r * ldo + n;
-    *dst = accumulate ? *dst + s : s;
+    out[r * ldo + n] = s;
+  }
+}
+__global__ void __launch_bounds__(kT) k_sum_splits(const float* P, int S, long long rows, int N, int Nvalid, float* out, int ldo) {
+  __shared__ float part[256][16];
+  const int le = threadIdx.x & 15, z0 = threadIdx.x >> 4;
+  const long long tot = rows * Nvalid;
+  for (long long base = blockIdx.x * 16LL; base < tot; base += gridDim.x * 16LL) {
+    const long long e = std::min(base + le, tot - 1);
+    const long long r = e / Nvalid;
+    const int n = (int)(e - r * Nvalid);
+    float s = 0.f;
+    for (int zb = 0; zb < S; zb += 256) {
+      const int nz = min(256, S - zb);
+#pragma unroll 8
+      for (int z = z0; z < nz; z += 16) part[z][le] = P[((long long)(zb + z) * rows + r) * N + n];
+      __syncthreads();
+      if (z0 == 0) {
+#pragma unroll 8
+        for (int z = 0; z < nz; ++z) s += part[z][le];
+      }
+      __syncthreads();
+    }
+    if (z0 == 0 && base + le < tot) out[r * ldo + n] = s;
   }
 }
 
@@ -601,13 +930,20 @@ __global__ void k_col2im_gelu(const float* dcol, int B, int n, int Ci, int Kp, c
   }
 }
 
-// W [rows][K] fp32 (flat parameter block) -> Wb [rows][Kp] bf16 with zero padding
-__global__ void k_pack(const float* W, int rows, int K, int Kp, bf16* Wb) {
-  const long long tot = (long long)rows * Kp;
+// layer blockIdx.y: W [rows][K] fp32 (flat parameter block) -> Wb [rows][Kp] bf16 with zero padding
+struct PackArgs {
+  const float* W[6];
+  bf16* Wb[6];
+  int rows[6], K[6], Kp[6];
+};
+__global__ void k_pack(PackArgs a) {
+  const int l = blockIdx.y;
+  const int K = a.K[l], Kp = a.Kp[l];
+  const long long tot = (long long)a.rows[l] * Kp;
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < tot; e += (long long)gridDim.x * blockDim.x) {
     const long long r = e / Kp;
     const int k = (int)(e - r * Kp);
-    Wb[e] = k < K ? to_bf16(W[r * K + k]) : (bf16)0;
+    a.Wb[l][e] = k < K ? to_bf16(a.W[l][r * K + k]) : (bf16)0;
   }
 }
 
@@ -655,9 +991,26 @@ __global__ void k_check(const uint8_t* phase, long long Nv, const float* lm, con
                         const float* C2, float tol, float lo, float hi, float max_spread, int* ok, float* spread_out) {
   __shared__ double red[kT];
   const int b = blockIdx.x;
-  double cnt = 0.0;
-  for (long long v = threadIdx.x; v < Nv; v += blockDim.x) cnt += phase[(long long)b * Nv + v] ? 1.0 : 0.0;
-  red[threadIdx.x] = cnt;
+  // 16 phase ids per load where the map is aligned (Nv is a multiple of 4096)
+  const uint8_t* pb = phase + (long long)b * Nv;
+  long long ones = 0;
+  if ((reinterpret_cast<uintptr_t>(pb) & 15u) == 0) {
+    const uint4* p4 = reinterpret_cast<const uint4*>(pb);
+#pragma unroll 4
+    for (long long v = threadIdx.x; v < Nv / 16; v += blockDim.x) {
+      const uint4 q = p4[v];
+      const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        // bit 7 of each byte: the byte is not zero
+        const uint32_t nz = ((wd[i] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | wd[i];
+        ones += __popc(nz & 0x80808080u);
+      }
+    }
+  } else {
+    for (long long v = threadIdx.x; v < Nv; v += blockDim.x) ones += pb[v] ? 1 : 0;
+  }
+  red[threadIdx.x] = (double)ones;
   __syncthreads();
   for (int s = kT / 2; s > 0; s >>= 1) {
     if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
@@ -817,14 +1170,13 @@ void plan(const fft_homog_cnn_desc* d, Plan* L) {
   size_t maxact = 0, maxcol = 0;
   for (int l = 1; l <= 4; ++l) {
     const long long Ml = Bm * (long long)L->edge[l] * L->edge[l] * L->edge[l];
-    // block 1 always expands its operand; blocks 2-4 only when their input channels are not a
-    // multiple of 8 (else the GEMMs gather it, implicit_conv)
-    const bool expand = l == 1 || ch[l - 1] % 8 != 0;
-    L->o_col[l] = take(expand ? (size_t)Ml * L->Kp[l] * 2 : 0);
+    // block 1 keeps its taps as bits; blocks 2-4 expand their operand only when their input channels
+    // are not a multiple of 8 (else the GEMMs gather it, implicit_conv)
+    L->o_col[l] = take(l == 1 ? (size_t)Ml * 4 : ch[l - 1] % 8 != 0 ? (size_t)Ml * L->Kp[l] * 2 : 0);
     L->o_pre[l] = take((size_t)Ml * ch[l] * 4);
     L->o_act[l] = take((size_t)Ml * ch[l] * 2);
     maxact = std::max(maxact, (size_t)Ml * ch[l]);
-    if (l >= 2) maxcol = std::max(maxcol, (size_t)Ml * L->Kp[l]);
+    if (l >= 2 && !(ch[l - 1] % 8 == 0 && ch[l] % 8 == 0)) maxcol = std::max(maxcol, (size_t)Ml * L->Kp[l]);
   }
   maxact = std::max(maxact, (size_t)Bm * std::max(d->hidden, L->Kp[5]));
   L->o_x5 = take((size_t)Bm * L->Kp[5] * 2);
@@ -844,8 +1196,8 @@ void plan(const fft_homog_cnn_desc* d, Plan* L) {
     const long long Ml = Bm * (long long)L->edge[l] * L->edge[l] * L->edge[l];
     sc = std::max(sc, (size_t)splits_for((int)Ml, 4096) * L->rows[l] * L->Kp[l]);
   }
-  sc = std::max(sc, (size_t)splits_for((int)Bm, 4096) * d->hidden * L->Kp[5]);
-  sc = std::max(sc, (size_t)splits_for((int)Bm, 4096) * d->n_out * d->hidden);
+  sc = std::max(sc, (size_t)d->hidden * L->Kp[5]);
+  sc = std::max(sc, (size_t)d->n_out * d->hidden);
   sc = std::max(sc, (size_t)Bm * std::max(L->Kp[5], std::max(d->hidden, d->n_out)));
   L->scratch_floats = sc;
   L->o_scratch = take(sc * 4);
@@ -878,50 +1230,71 @@ int check_batch(fft_homog_cnn_t* h, int B) { return (B >= 1 && B <= h->d.max_bat
 // 16-byte loads of 8 channels
 bool implicit_conv(const fft_homog_cnn_t* h, int l) { return l > 1 && h->d.channels[l - 1] % 8 == 0; }
 ConvOperand conv_operand(const fft_homog_cnn_t* h, int l) {
-  return ConvOperand{h->act[l - 1], h->edge[l - 1], h->edge[l], h->d.channels[l - 1]};
+  return ConvOperand{h->act[l - 1], h->edge[l - 1], h->d.channels[l - 1], make_div(h->edge[l]), make_div(h->d.channels[l - 1])};
 }
+// conv block l > 1 whose input gradient is one product per parity class (k_dgrad): rows of 8 channels on
+// both sides; else the products of all taps are formed in memory and gathered
+bool implicit_dgrad(const fft_homog_cnn_t* h, int l) { return implicit_conv(h, l) && h->d.channels[l] % 8 == 0; }
 
-// forward pass of B samples into h->y (before output scaling is applied by the caller path)
-int forward(fft_homog_cnn_t* h, const uint8_t* phase, const float* feat, int B) {
+// forward pass of B samples into h->y (before output scaling is applied by the caller path).  train:
+// keep what the gradient needs (pre-activations, block 1's taps)
+int forward(fft_homog_cnn_t* h, const uint8_t* phase, const float* feat, int B, bool train) {
   const int* ch = h->d.channels;
   CK(hipMemsetAsync(h->flag, 0, sizeof(int), h->s));
   for (int l = 1; l <= 4; ++l) {
     const int n = h->edge[l - 1];
-    const long long Ml = (long long)B * h->edge[l] * h->edge[l] * h->edge[l];
-    if (l == 1 || !implicit_conv(h, l)) {
-      if (l == 1)
-        hipLaunchKernelGGL(k_im2col_phase, dim3(blocks(Ml)), dim3(kT), 0, h->s, phase, B, n, h->Kp[1], h->col[1], h->flag);
-      else
-        hipLaunchKernelGGL(k_im2col, dim3(blocks(Ml * 27)), dim3(kT), 0, h->s, h->act[l - 1], B, n, ch[l - 1], h->Kp[l],
-                           h->col[l]);
+    const int Ml = (int)((long long)B * h->edge[l] * h->edge[l] * h->edge[l]);
+    // the pooling reads block 4's pre-activations, nothing its activations
+    float* pre = train || l == 4 ? h->pre[l] : nullptr;
+    bf16* act = l < 4 ? h->act[l] : nullptr;
+    const float* bias = h->p + h->offB[l];
+    if (l == 1) {
+      hipLaunchKernelGGL(k_conv_phase, dim3((Ml + kT - 1) / kT), dim3(kT), 0, h->s, phase, Ml, n, make_div(h->edge[1]),
+                         h->Wb[1], ch[1], bias, pre, act, train ? (uint8_t*)h->col[1] : nullptr, h->flag);
       CK(hipGetLastError());
-      CK(gemm((int)Ml, ch[l], h->Kp[l], h->col[l], h->Kp[l], 1, h->Wb[l], h->Kp[l], 1, h->pre[l], 1, h->s));
+    } else if (implicit_conv(h, l)) {
+      CK(gemm_conv_forward(Ml, ch[l], h->Kp[l], conv_operand(h, l), h->Wb[l], bias, pre, act, h->s));
     } else {
-      CK(gemm_conv_forward((int)Ml, ch[l], h->Kp[l], conv_operand(h, l), h->Wb[l], h->pre[l], h->s));
+      hipLaunchKernelGGL(k_im2col, dim3(blocks(Ml * 27LL)), dim3(kT), 0, h->s, h->act[l - 1], B, n, ch[l - 1], h->Kp[l],
+                         h->col[l]);
+      CK(hipGetLastError());
+      CK(gemm(Ml, ch[l], h->Kp[l], h->col[l], h->Kp[l], 1, h->Wb[l], h->Kp[l], 1, pre, 1, h->s, bias, act));
     }
-    hipLaunchKernelGGL(k_bias_gelu, dim3(blocks(Ml * ch[l])), dim3(kT), 0, h->s, h->pre[l], h->p + h->offB[l], Ml, ch[l],
-                       h->act[l]);
-    CK(hipGetLastError());
   }
   const int V = h->edge[4] * h->edge[4] * h->edge[4];
   hipLaunchKernelGGL(k_pool_concat, dim3(blocks((long long)B * h->Kp[5])), dim3(kT), 0, h->s, h->pre[4], B, V, ch[4], feat,
                      h->d.n_feat, h->Kp[5], h->x5);
   CK(hipGetLastError());
-  CK(gemm(B, h->d.hidden, h->Kp[5], h->x5, h->Kp[5], 1, h->Wb[5], h->Kp[5], 1, h->pre5, 1, h->s));
-  hipLaunchKernelGGL(k_bias_gelu, dim3(blocks((long long)B * h->d.hidden)), dim3(kT), 0, h->s, h->pre5, h->p + h->offB[5],
-                     (long long)B, h->d.hidden, h->h);
-  CK(hipGetLastError());
+  CK(gemm(B, h->d.hidden, h->Kp[5], h->x5, h->Kp[5], 1, h->Wb[5], h->Kp[5], 1, train ? h->pre5 : nullptr, 1, h->s,
+          h->p + h->offB[5], h->h));
   CK(gemm(B, h->d.n_out, h->d.hidden, h->h, h->d.hidden, 1, h->Wb[6], h->Kp[6], 1, h->scratch, 1, h->s));
   return FFT_HOMOG_OK;
 }
 
 int refresh_weights(fft_homog_cnn_t* h) {
-  for (int l = 1; l <= 6; ++l) {
-    hipLaunchKernelGGL(k_pack, dim3(blocks((long long)h->rows[l] * h->Kp[l])), dim3(kT), 0, h->s, h->p + h->offW[l],
-                       h->rows[l], h->Kc[l], h->Kp[l], h->Wb[l]);
-    CK(hipGetLastError());
+  PackArgs a;
+  long long most = 0;
+  for (int l = 0; l < 6; ++l) {
+    a.W[l] = h->p + h->offW[l + 1];
+    a.Wb[l] = h->Wb[l + 1];
+    a.rows[l] = h->rows[l + 1];
+    a.K[l] = h->Kc[l + 1];
+    a.Kp[l] = h->Kp[l + 1];
+    most = std::max(most, (long long)a.rows[l] * a.Kp[l]);
   }
+  hipLaunchKernelGGL(k_pack, dim3(blocks(most), 6), dim3(kT), 0, h->s, a);
+  CK(hipGetLastError());
   return FFT_HOMOG_OK;
+}
+
+// out = the sum of S split products
+hipError_t sum_splits(fft_homog_cnn_t* h, int S, long long rows, int N, int Nvalid, float* out) {
+  const unsigned nb = (unsigned)std::min<long long>((rows * Nvalid + 15) / 16, 1 << 20);
+  if (S <= kFewSplits)
+    hipLaunchKernelGGL(k_sum_few_splits, dim3(blocks(rows * Nvalid)), dim3(kT), 0, h->s, h->scratch, S, rows, N, Nvalid, out, Nvalid);
+  else
+    hipLaunchKernelGGL(k_sum_splits, dim3(nb), dim3(kT), 0, h->s, h->scratch, S, rows, N, Nvalid, out, Nvalid);
+  return hipGetLastError();
 }
 
 int read_flag(fft_homog_cnn_t* h) {
@@ -1051,7 +1424,7 @@ int fft_homog_cnn_forward(fft_homog_cnn_t* h, const uint8_t* phase, const float*
   if (!h || !phase || !out || (h->d.n_feat > 0 && !feat)) return FFT_HOMOG_EINVAL;
   if (check_batch(h, batch)) return FFT_HOMOG_EINVAL;
   CK(hipEventRecord(h->e0, h->s));
-  int rc = forward(h, phase, feat, batch);
+  int rc = forward(h, phase, feat, batch, false);
   if (rc) return rc;
   hipLaunchKernelGGL(k_output, dim3(blocks((long long)batch * h->d.n_out)), dim3(kT), 0, h->s, h->scratch,
                      h->p + h->offB[6], out_scale, out_offset, batch, h->d.n_out, out);
@@ -1071,7 +1444,7 @@ int fft_homog_cnn_loss_grad(fft_homog_cnn_t* h, const uint8_t* phase, const floa
   const int* ch = h->d.channels;
   const int O = h->d.n_out, H = h->d.hidden;
   CK(hipEventRecord(h->e0, h->s));
-  int rc = forward(h, phase, feat, B);
+  int rc = forward(h, phase, feat, B, true);
   if (rc) return rc;
   hipLaunchKernelGGL(k_output, dim3(blocks((long long)B * O)), dim3(kT), 0, h->s, h->scratch, h->p + h->offB[6],
                      nullptr, nullptr, B, O, h->y);
@@ -1079,8 +1452,7 @@ int fft_homog_cnn_loss_grad(fft_homog_cnn_t* h, const uint8_t* phase, const floa
   CK(hipGetLastError());
   // dense output layer: dW6 = dy^T h, db6 = sum dy, dh = dy W6
   CK(gemm(O, H, B, h->dyb, 1, O, h->h, 1, H, h->scratch, 1, h->s));
-  hipLaunchKernelGGL(k_sum_splits, dim3(blocks((long long)O * H)), dim3(kT), 0, h->s, h->scratch, 1, (long long)O, H, H,
-                     h->g + h->offW[6], H, 0);
+  CK(sum_splits(h, 1, O, H, H, h->g + h->offW[6]));
   CK(colsum(h, h->dy32, B, O, h->g + h->offB[6]));
   CK(gemm(B, H, O, h->dyb, O, 1, h->Wb[6], 1, h->Kp[6], h->scratch, 1, h->s));
   hipLaunchKernelGGL(k_gelu_back, dim3(blocks((long long)B * H)), dim3(kT), 0, h->s, h->scratch, H, h->pre5, (long long)B,
@@ -1089,8 +1461,7 @@ int fft_homog_cnn_loss_grad(fft_homog_cnn_t* h, const uint8_t* phase, const floa
   // hidden layer: dW5 = dpre5^T x5, db5, dx5 = dpre5 W5
   const int K5 = h->Kc[5], Kp5 = h->Kp[5];
   CK(gemm(H, Kp5, B, h->dAb, 1, H, h->x5, 1, Kp5, h->scratch, 1, h->s));
-  hipLaunchKernelGGL(k_sum_splits, dim3(blocks((long long)H * K5)), dim3(kT), 0, h->s, h->scratch, 1, (long long)H, Kp5, K5,
-                     h->g + h->offW[5], K5, 0);
+  CK(sum_splits(h, 1, H, Kp5, K5, h->g + h->offW[5]));
   CK(colsum(h, h->dA, B, H, h->g + h->offB[5]));
   CK(gemm(B, ch[4], H, h->dAb, H, 1, h->Wb[5], 1, Kp5, h->scratch, 1, h->s));
   const int V = h->edge[4] * h->edge[4] * h->edge[4];
@@ -1105,29 +1476,46 @@ int fft_homog_cnn_loss_grad(fft_homog_cnn_t* h, const uint8_t* phase, const floa
   for (int l = 4; l >= 1; --l) {
     const long long Ml = (long long)B * h->edge[l] * h->edge[l] * h->edge[l];
     const int S = splits_for((int)Ml, 4096);
-    if (l > 1 && implicit_conv(h, l))
-      CK(gemm_conv_wgrad(ch[l], h->Kp[l], (int)Ml, db, conv_operand(h, l), h->scratch, S, h->s));
-    else
-      CK(gemm(ch[l], h->Kp[l], (int)Ml, db, 1, ch[l], h->col[l], 1, h->Kp[l], h->scratch, S, h->s));
-    int Sused;
-    {
-      int chunk = ((int)Ml + S - 1) / S;
-      chunk = (chunk + BK - 1) / BK * BK;
-      Sused = ((int)Ml + chunk - 1) / chunk;
+    int used = 1;
+    if (l == 1) {
+      CK(gemm_conv_wgrad(ch[l], h->Kp[l], (int)Ml, db, nullptr, (const uint8_t*)h->col[1], h->scratch, S, h->s, &used));
+    } else if (implicit_conv(h, l)) {
+      const ConvOperand cv = conv_operand(h, l);
+      CK(gemm_conv_wgrad(ch[l], h->Kp[l], (int)Ml, db, &cv, nullptr, h->scratch, S, h->s, &used));
+    } else {
+      CK(gemm(ch[l], h->Kp[l], (int)Ml, db, 1, ch[l], h->col[l], 1, h->Kp[l], h->scratch, S, h->s, nullptr, nullptr, &used));
     }
-    hipLaunchKernelGGL(k_sum_splits, dim3(blocks((long long)ch[l] * h->Kc[l])), dim3(kT), 0, h->s, h->scratch, Sused,
-                       (long long)ch[l], h->Kp[l], h->Kc[l], h->g + h->offW[l], h->Kc[l], 0);
+    CK(sum_splits(h, used, ch[l], h->Kp[l], h->Kc[l], h->g + h->offW[l]));
     CK(colsum(h, d32, Ml, ch[l], h->g + h->offB[l]));
-    if (l > 1) {
+    if (l == 1) break;
+    const int nin = h->edge[l - 1];
+    if (implicit_dgrad(h, l)) {
+      DgradArgs a;
+      a.M = (int)Ml;
+      a.Ci = ch[l - 1];
+      a.Co = ch[l];
+      a.Kp = h->Kp[l];
+      a.n = nin;
+      a.m = make_div(h->edge[l]);
+      a.co = make_div(round32(ch[l]));
+      a.dpre = db;
+      a.W = h->Wb[l];
+      a.pre = h->pre[l - 1];
+      a.d32 = n32;
+      a.db = nb;
+      const unsigned gx = (unsigned)((Ml + BM - 1) / BM);
+      const dim3 grid(gx, (a.Ci + BN - 1) / BN, 8);
+      if (a.Ci <= 32) hipLaunchKernelGGL(k_dgrad<true>, grid, dim3(kT), 0, h->s, a);
+      else hipLaunchKernelGGL(k_dgrad<false>, grid, dim3(kT), 0, h->s, a);
+    } else {
       CK(gemm((int)Ml, h->Kp[l], ch[l], db, ch[l], 1, h->Wb[l], 1, h->Kp[l], h->dcol, 1, h->s));
-      const int nin = h->edge[l - 1];
       const long long Min = (long long)B * nin * nin * nin;
       hipLaunchKernelGGL(k_col2im_gelu, dim3(blocks(Min * ch[l - 1])), dim3(kT), 0, h->s, h->dcol, B, nin, ch[l - 1],
                          h->Kp[l], h->pre[l - 1], n32, nb);
-      CK(hipGetLastError());
-      std::swap(d32, n32);
-      std::swap(db, nb);
     }
+    CK(hipGetLastError());
+    std::swap(d32, n32);
+    std::swap(db, nb);
   }
   if (grad) CK(hipMemcpyAsync(grad, h->g, h->P * 4, hipMemcpyDeviceToDevice, h->s));
   CK(hipMemcpyAsync(h->h_loss, h->lossd, 4, hipMemcpyDeviceToHost, h->s));
