@@ -31,11 +31,11 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-KERNELS = ["xfwd_cgop", "reduce_pq", "y_fwd", "outer_project", "y_inv", "xinv_cgupdate", "reduce_rr"]
+KERNELS = ["x_op", "reduce_pq", "y_fwd", "outer_fwd", "y_inv", "outer_inv", "reduce_rr"]
 
 
-CG_KERNEL_SOURCES = ["common.h", "dual.h", "fft_lds.h", "kernels.h", "kernels.hip", "launch_geometry.cpp", "materials.h",
-                     "pass_kernels.h"]
+CG_KERNEL_SOURCES = ["common.h", "dual.h", "fft_lds.h", "kernels.h", "kernels.hip", "kernels_fixed.hip",
+                     "launch_geometry.cpp", "materials.h", "pass_kernels.h", "xpass_law.h", "xpass_nh.hip"]
 
 
 def kernel_source_hash():
@@ -72,27 +72,21 @@ def log(msg):
 
 
 def algorithmic_bytes_per_voxel(c, N, Nh, material_reads_strain=True, rows=False):
-    """HBM bytes per voxel each CG-iteration kernel must move at minimum (FP64).
+    """HBM bytes per voxel each kernel of an iteration of the 3D CG on displacements must move (FP64).
 
-    xfwd reads r, p, x, the linearisation point F and the phase id and writes
-    p, x and the half spectrum; xinv reads the half spectrum and r and writes r;
-    the y and outer passes read and write the half spectrum once.  rows: the 3D
-    finite-strain projection runs row by row, and between the y passes the
-    spectrum has two instead of three components per row of F (the forward y pass
-    reads 9 and writes 6 components, the outer pass reads and writes 6, the inverse
-    y pass reads 6 and writes 9).
+    The x pass reads and writes the half spectrum of c components and reads the
+    linearisation point F and the phase id; the y passes read and write the half
+    spectrum once; the forward outer pass reads it and reads and writes r (three
+    complex components per wavevector), the inverse one reads r, p, x and writes p, x
+    and the half spectrum.  rows: the finite-strain passes run row by row, and between
+    the y passes the spectrum has two instead of three components per row of F.
     """
     f = 8.0 * c               # one packed field
     s = 16.0 * c * Nh / N     # one half spectrum (nx/2+1 bins per row), per voxel
-    xfwd = 3 * f + (f if material_reads_strain else 0.0) + 1.0 + 2 * f + s
-    mid = 2 * s
-    outer = 2 * s
-    if rows:
-        mid = s + s * 2.0 / 3.0
-        outer = 2 * s * 2.0 / 3.0
-    xinv = s + 2 * f
-    return {"xfwd_cgop": xfwd, "reduce_pq": 0.0, "y_fwd": mid, "outer_project": outer, "y_inv": mid,
-            "xinv_cgupdate": xinv, "reduce_rr": 0.0}
+    u = 16.0 * 3 * Nh / N     # one displacement vector
+    inner = s * 2.0 / 3.0 if rows else s
+    return {"x_op": 2 * s + (f if material_reads_strain else 0.0) + 1.0, "reduce_pq": 0.0, "y_fwd": s + inner,
+            "outer_fwd": inner + 2 * u, "y_inv": inner + s, "outer_inv": inner + 5 * u, "reduce_rr": 0.0}
 
 
 # the survey's byte model of one CG iteration (c = 9, finite strain): 8 CG-vector fields, the

@@ -105,12 +105,15 @@ enum { FFT_HOMOG_FIELD_STRAIN = 0, FFT_HOMOG_FIELD_STRESS = 1, FFT_HOMOG_FIELD_E
 
 typedef struct fft_homog_desc {
   int ndim;          /* 2 or 3 */
-  int n[3];          /* grid points along x, y, z; each 1..1024.  Factors 2, 3, 5 run radix stages;
-                        other prime factors run a direct DFT stage of that length, or, when those
-                        lengths add up to more than 70 (outer axis) or 150 (x and y axes), the axis
-                        runs the chirp-z (Bluestein) transform through cyclic convolutions of a
-                        length m >= 2n - 1 with factors 2, 3, 5 (more LDS per sequence; if its
-                        buffers do not fit, every axis keeps the direct stages) */
+  int n[3];          /* grid points along x, y, z; each 1..1024.  Lengths with a compiled schedule run
+                        its radix stages.  Others of 17..128 run a folded dense DFT on the matrix
+                        cores, and so do those of 129..256 whose prime factors above 5 add up to more
+                        than 120 (2D) or 30 (3D).  The rest run radix stages for factors 2, 3, 5 and a
+                        direct DFT stage for each other prime factor, or, when those add up to more
+                        than 270 (outer axis) or 410 (x and y axes), the chirp-z (Bluestein)
+                        transform through cyclic convolutions of a length m >= 2n - 1 with factors 2,
+                        3, 5.  If the buffers of the dense DFT or of the chirp-z form do not fit, no
+                        axis runs it */
   double len[3];     /* cell edge lengths along x, y, z (> 0); wavevector xi = 2 pi k / len */
   int kinematics;    /* FFT_HOMOG_SMALL_STRAIN or FFT_HOMOG_FINITE_STRAIN */
   int material;      /* LINEAR_ELASTIC or J2_PLASTIC (small), NEO_HOOKEAN or STVK (finite); J2
@@ -330,12 +333,16 @@ int fft_homog_debug_cg_chunk(int iters, double rr0, double rr, double tol, int p
 /* Average device time (ms, HIP events on the handle's stream) of each kernel of one CG
  * iteration (section 3 operator, Appendix A linear solve), measured over `iters` iterations
  * of the linear solve G*(K:x) = -G*(K:E_1) at the current state, batch 1, with the
- * convergence test disabled.  ms[7] receives, in launch order: x-pass forward (CG vector
- * update, K:p, x-FFT, partial <p,K:p>), a slot for a separate <p,K:p> reduction (0: one block
- * of the outer pass sums <p,K:p> and sets alpha), y-pass forward, outer pass (outer-axis FFT,
- * G-hat, inverse FFT), y-pass inverse, x-pass inverse (inverse x-FFT, residual update, partial
- * <r,r>), <r,r> reduction, beta and the convergence test; 2D grids report 0 for the y passes.
- * Leaves the strain state unchanged. */
+ * convergence test disabled.  ms[7] receives, 3D grids with tol_cg >= 1e-11 (the CG on
+ * displacements): x pass (inverse x-FFT, K:p, x-FFT, partial <p,K:p>), a slot for a separate
+ * <p,K:p> reduction (0: one block of the forward y pass sums <p,K:p> and sets alpha), y-pass
+ * forward, forward outer pass (outer-axis FFT, displacement, residual update, partial <r,r>),
+ * y-pass inverse, inverse outer pass (update of x and p, strain, inverse FFT; an iteration starts
+ * with it), <r,r> reduction, beta and the convergence test.  Others (the CG on strain fields), in
+ * launch order: x-pass forward (CG vector update, K:p, x-FFT, partial <p,K:p>), the same slot (one
+ * block of the outer pass sums), y-pass forward, outer pass (outer-axis FFT, G-hat, inverse FFT),
+ * y-pass inverse, x-pass inverse (inverse x-FFT, residual update, partial <r,r>), <r,r> reduction;
+ * 2D grids report 0 for the y passes.  Leaves the strain state unchanged. */
 int fft_homog_debug_time_cg(fft_homog_t* h, int iters, double* ms);
 
 /* Sampled kernel timing inside the solver's own CG loops (solve, tangent and adjoint calls):
@@ -346,7 +353,7 @@ int fft_homog_debug_time_cg(fft_homog_t* h, int iters, double* ms);
  * EINVAL for every < 0. */
 int fft_homog_set_kernel_timing(fft_homog_t* h, int every);
 /* Average device time (ms) of each launch of the sampled CG iterations since the last
- * fft_homog_set_kernel_timing, in the launch order and layout of fft_homog_debug_time_cg's
+ * fft_homog_set_kernel_timing, in the layout of fft_homog_debug_time_cg's
  * ms[7]: the time from the previous launch's end event to this launch's end event, so it
  * includes the launch's dispatch.  *samples receives the number of sampled iterations (ms is
  * all zero when it is 0). */

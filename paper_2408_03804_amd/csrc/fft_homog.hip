@@ -54,13 +54,12 @@ struct Layout {
 };
 
 // Chirp-z thresholds (sum of the direct stages' prime lengths above 5, see make_plan), measured per
-// pass from CG-iteration kernel times on MI355X with both forms, lengths 31 to 511 in 2D and 3D:
-// the outer pass (G-hat between a forward and an inverse transform) gains from 80 (511 = 7 * 73)
-// and 97 on and loses at 61 and at 36 (299 = 13 * 23); the x passes break even at 127 and gain
-// at 199, the y pass loses at 97.  The x and y passes hold more sequences per block, which the
-// chirp-z buffers (about twice the axis length) crowd out.
-constexpr int kChirpOuter = 70;
-constexpr int kChirpRows = 150;
+// pass from CG-iteration kernel times of n x n grids with both forms, direct against chirp-z in us:
+// the outer pass (G-hat between a forward and an inverse transform) 37 / 58 at 107 (321 = 3 * 107),
+// 48 / 55 at 257, 54 / 52 at 283 and 57 / 50 at 307; the two x passes together 68 / 93 at 199,
+// 103 / 108 at 401, 108 / 104 at 439 and 123 / 101 at 499.
+constexpr int kChirpOuter = 270;
+constexpr int kChirpRows = 410;
 
 // Transforms the axes of a layout may take: radix and direct prime stages only, also the chirp-z
 // form, also the folded dense DFT.
@@ -70,7 +69,7 @@ enum PlanSet { PLANS_DIRECT = 0, PLANS_CHIRP = 1, PLANS_DENSE = 2 };
 bool make_plans(const fft_homog_desc* d, int plans, AxisPlan* pl, Geom* g) {
   for (int a = 0; a < 3; ++a) {
     const int n = a < d->ndim ? d->n[a] : 1;
-    const bool dense = plans >= PLANS_DENSE && dense_len(n);
+    const bool dense = plans >= PLANS_DENSE && dense_len(n, d->ndim);
     const int lim = plans < PLANS_CHIRP || dense ? 0 : a == d->ndim - 1 ? kChirpOuter : kChirpRows;
     if (!make_plan(n, &pl[a], lim)) return false;
     pl[a].dense = dense ? 1 : 0;

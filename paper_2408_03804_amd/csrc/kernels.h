@@ -123,14 +123,15 @@ bool inplace_ok(const AxisPlan& pl, int nseq);
 // length when the direct stages' prime lengths other than 2, 3 and 5 sum to more than chirp_above
 // (0: never); table pointers left null.  False if n has no factorisation within kMaxStages stages.
 bool make_plan(int n, AxisPlan* pl, int chirp_above);
-// true if an axis of length n runs the folded dense DFT: every length without a compiled schedule from
-// 17 (below, one row tile would be mostly padding) to kDenseMax points.  Measured against the radix,
-// direct prime and chirp-z stages it replaces: a CG iteration's passes at 199 points (prime) 26 + 40 +
-// 24 us -> 14 + 23 + 13 us, at 33^3 20 + 15 + 20 us (y, outer, y) -> 13 + 9 + 13 us; its cost per
-// element grows with n, and at 299 = 13 * 23 points the direct stages were faster (25 against 29 ms
-// per solve).
+// true if an axis of length n of a grid of ndim dimensions runs the folded dense DFT: lengths without a
+// compiled schedule from 17 (below, one row tile would be mostly padding) to kDenseMax points, beyond
+// kDenseAll only with a large prime factor.  Measured against the radix and direct prime stages, us per
+// CG iteration (finite strain): 33^3 80 against 97, 57^3 114 / 161, 91^3 298 / 402, 119^3 616 / 864,
+// 119^2 54 / 56; but 143^2 (11 x 13) 68 / 58, 221^2 80 / 63, 143^3 1638 / 1545, as its cost per element
+// grows with n.  In 2D it is even at a prime of 151 and loses at 89 (178^2 75 / 68).
+constexpr int kDenseAll = 128;
 constexpr int kDenseMax = 256;
-bool dense_len(int n);
+bool dense_len(int n, int ndim);
 size_t dense_elems(int n);  // entries of its operand-fragment table
 // LDS rows per sequence of the x, mid and outer transforms of the plans pl[0..ndim-1]
 void set_lds_lens(Geom* g, const AxisPlan* pl);

@@ -703,7 +703,7 @@ hipError_t set_smem_limits(const Geom& g, int mat, size_t bytes) {
   if (e == hipSuccess && (g.lx != g.nx || g.lo != g.n_outer || (g.ndim == 3 && g.lm != g.ny)))
     e = set_smem_limits_chirp(g, bytes);
   if (e == hipSuccess) e = set_smem_limits_fixed(g, bytes);
-  if (e == hipSuccess && (dense_len(g.nx) || dense_len(g.ny) || dense_len(g.nz))) e = set_smem_limits_dense(g, bytes);
+  if (e == hipSuccess && (dense_len(g.nx, g.ndim) || dense_len(g.ny, g.ndim) || dense_len(g.nz, g.ndim))) e = set_smem_limits_dense(g, bytes);
   return e;
 }
 

@@ -101,6 +101,14 @@ bool factorize(int n, int* radix, int* nst) {
   return m == 1;
 }
 
+// sum of the direct stages' prime lengths above 5
+int direct_sum(const int* rad, int ns) {
+  int sum = 0;
+  for (int st = 0; st < ns; ++st)
+    if (rad[st] != 2 && rad[st] != 3 && rad[st] != 4 && rad[st] != 5 && rad[st] != 8 && rad[st] != 16) sum += rad[st];
+  return sum;
+}
+
 // smallest length >= 2n - 1 whose only prime factors are 2, 3 and 5
 static int chirp_len(int n) {
   for (int m = 2 * n - 1;; ++m) {
@@ -119,9 +127,7 @@ bool make_plan(int n, AxisPlan* pl, int chirp_above) {
   pl->dense = 0;
   int rad[kMaxStages], ns = 0;
   const bool ok = factorize(n, rad, &ns);
-  int direct = ok ? 0 : 1 << 30;  // sum of the direct stages' prime lengths
-  for (int st = 0; st < ns; ++st)
-    if (rad[st] != 2 && rad[st] != 3 && rad[st] != 4 && rad[st] != 5 && rad[st] != 8 && rad[st] != 16) direct += rad[st];
+  const int direct = ok ? direct_sum(rad, ns) : 1 << 30;
   if (chirp_above > 0 && direct > chirp_above) {
     const int m = chirp_len(n);
     int mrad[kMaxStages], mns = 0;
@@ -138,7 +144,12 @@ bool make_plan(int n, AxisPlan* pl, int chirp_above) {
   return true;
 }
 
-bool dense_len(int n) { return n >= 17 && n <= kDenseMax && fixed_nstages(n) == 0; }
+bool dense_len(int n, int ndim) {
+  if (n < 17 || n > kDenseMax || fixed_nstages(n) != 0) return false;
+  if (n <= kDenseAll) return true;
+  int rad[kMaxStages], ns = 0;
+  return !factorize(n, rad, &ns) || direct_sum(rad, ns) > (ndim == 2 ? 120 : 30);
+}
 size_t dense_elems(int n) { return (size_t)dense_rows(n) * dense_steps(n) * 64; }
 
 size_t plan_table_elems(const AxisPlan& pl) {
