@@ -257,7 +257,7 @@ int fft_homog_autotune(fft_homog_t* h, int reps, int shape[7]);
  * and the spectrum by s, 2 s, 3 s and 4 s bytes.  How the x passes' streams spread over the HBM
  * channels depends on that placement and on the physical pages behind the workspace, so the
  * candidates {0, 256 B, 16 KiB, 256 KiB, 2 MiB, 4 MiB} are timed on this handle (reps launches of
- * the forward and inverse x passes each, work vectors zeroed) and the fastest is kept if it beats
+ * the x pass, or the forward and inverse ones, each, work vectors zeroed) and the fastest is kept if it beats
  * the current one by 2 %.  Results do not depend on the placement (same kernels, same reduction
  * order): only the time does.  *stagger (may be NULL) receives the chosen s.  On smaller grids
  * the only candidate is 0.  Call it between solves, not during one (the work vectors are

@@ -1,7 +1,8 @@
 """The folded dense DFT on the FP64 matrix cores (axis lengths without a compiled radix schedule).
 
 Real transforms against numpy at the lengths where its tiles change: around multiples of 32 (row
-tiles of 16 on half the length), the smallest and the largest length it takes, odd, even and prime,
+tiles of 16 on half the length), the smallest and the largest length it takes, odd, even and prime
+(130 and 255, without a large prime factor, are the direct stages' in 2D or in both),
 on the x, the y and the outer axis, with tiles of one and of several sequences.  Tolerance, relative
 2-norm: each axis sums n/2 <= 128 products in chains of 8, about (8 + n/32)/2 roundings of 1.1e-16
 each way of growing, and the spectrum passes through three axes: 3 x 6 x 1.1e-16 = 2e-15.
