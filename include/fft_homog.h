@@ -323,6 +323,10 @@ int fft_homog_debug_apply_operator(fft_homog_t* h, const double* p, double* q, i
  * iterate), EBREAKDOWN if <p, K:p> <= 0 before `iters`, EUNSUPPORTED on multi-cell handles. */
 int fft_homog_debug_cg(fft_homog_t* h, int iters, double* x_out, double* r_out);
 
+/* The transform each of the descriptor's ndim axes runs: 0 radix and direct prime stages, 1 chirp-z,
+ * 2 folded dense DFT (host only, no handle).  Errors as fft_homog_workspace_size. */
+int fft_homog_debug_axis_plans(const fft_homog_desc* d, int kinds[3]);
+
 /* Pure host function: the number of CG iterations the solver enqueues before its next host
  * check for a single right-hand side that has run `iters` iterations with residual norms
  * rr0 = <b,b>, rr = <r,r> and relative tolerance tol, given the iteration count and <r,r> at

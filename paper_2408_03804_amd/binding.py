@@ -81,7 +81,7 @@ EXPORTS = [
     "fft_homog_destroy", "fft_homog_strerror", "fft_homog_last_error",
     "fft_homog_debug_constitutive", "fft_homog_debug_rfft", "fft_homog_debug_irfft",
     "fft_homog_debug_project", "fft_homog_debug_apply_operator", "fft_homog_debug_cg",
-    "fft_homog_debug_cg_chunk", "fft_homog_debug_time_cg",
+    "fft_homog_debug_cg_chunk", "fft_homog_debug_time_cg", "fft_homog_debug_axis_plans",
     "fft_homog_set_kernel_timing", "fft_homog_get_kernel_timing",
     "fft_homog_get_launch_shape", "fft_homog_set_launch_shape", "fft_homog_autotune", "fft_homog_tune_placement",
     "fft_homog_set_placement",
@@ -125,6 +125,7 @@ def load_library(path=LIB_PATH):
         "fft_homog_debug_cg": (I, [P, I, P, P]),
         "fft_homog_debug_cg_chunk": (I, [I, D, D, D, I, D]),
         "fft_homog_debug_time_cg": (I, [P, I, DP]),
+        "fft_homog_debug_axis_plans": (I, [ctypes.POINTER(Desc), ctypes.POINTER(I)]),
         "fft_homog_set_kernel_timing": (I, [P, I]),
         "fft_homog_get_kernel_timing": (I, [P, DP, ctypes.POINTER(ctypes.c_longlong)]),
         "fft_homog_get_launch_shape": (I, [P, ctypes.POINTER(I)]),
@@ -193,6 +194,16 @@ def fft_homog_workspace_size(desc):
     if rc:
         raise FFTHomogError(rc, L.fft_homog_strerror(rc).decode())
     return nbytes.value
+
+
+def fft_homog_debug_axis_plans(desc):
+    """Transforms of the axes, in the grid's order (z, y, x): "direct", "chirp" or "dense"."""
+    L = load_library()
+    kinds = (ctypes.c_int * 3)()
+    rc = L.fft_homog_debug_axis_plans(ctypes.byref(desc), kinds)
+    if rc:
+        raise FFTHomogError(rc, L.fft_homog_strerror(rc).decode())
+    return tuple(("direct", "chirp", "dense")[k] for k in kinds[:desc.ndim])[::-1]
 
 
 class FFTHomog:

@@ -1435,6 +1435,19 @@ int fft_homog_debug_cg(fft_homog_t* h, int iters, double* x_out, double* r_out) 
   return FFT_HOMOG_OK;
 }
 
+int fft_homog_debug_axis_plans(const fft_homog_desc* d, int* kinds) {
+  if (!kinds) return FFT_HOMOG_EINVAL;
+  Layout L;
+  const int rc = make_layout(d, &L);
+  if (rc) return rc;
+  Geom g;
+  AxisPlan pl[3];
+  make_geom(d, &g);
+  make_plans(d, L.plans, pl, &g);
+  for (int a = 0; a < d->ndim; ++a) kinds[a] = pl[a].dense ? PLANS_DENSE : pl[a].m > 0 ? PLANS_CHIRP : PLANS_DIRECT;
+  return FFT_HOMOG_OK;
+}
+
 int fft_homog_debug_cg_chunk(int iters, double rr0, double rr, double tol, int prev_iters, double prev_rr) {
   return cg_chunk_length(iters, rr0, rr, tol, prev_iters, prev_rr);
 }
