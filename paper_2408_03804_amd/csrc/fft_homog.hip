@@ -1733,7 +1733,6 @@ int fft_homog_project_noalloc(const fft_homog_desc* d, const double* in, double*
   Layout L;
   Geom g;
   AxisPlan pl[3];
-  size_t tw_off[3] = {0, 0, 0};
   size_t spec_off = 0, need = 0;
   // scratch: FFT tables of the axes, then the half spectrum [batch][c][z][y][pitch]; a request that
   // only the dense DFT's tables push beyond the scratch runs without it
@@ -1742,12 +1741,8 @@ int fft_homog_project_noalloc(const fft_homog_desc* d, const double* in, double*
     if (rc) return create_fail(rc, "invalid or unsupported descriptor", hipSuccess);
     make_geom(d, &g);
     make_plans(d, L.plans, pl, &g);
-    size_t off = 0;
-    for (int a = 0; a < d->ndim; ++a) {
-      tw_off[a] = off;
-      off = align_up(off + plan_table_elems(pl[a]) * sizeof(double2));
-    }
-    spec_off = off;
+    spec_off = 0;
+    for (int a = 0; a < d->ndim; ++a) spec_off += plan_table_stride(pl[a]) * sizeof(double2);
     need = spec_off + (size_t)batch * g.c * g.Nh * sizeof(double2);
     if (need <= kNoAllocScratchBytes) break;
   }
@@ -1761,7 +1756,8 @@ int fft_homog_project_noalloc(const fft_homog_desc* d, const double* in, double*
   hipError_t e = noalloc_scratch_address((void**)&base);
   if (e != hipSuccess) return create_fail(FFT_HOMOG_EDEVICE, "hipGetSymbolAddress(scratch)", e);
   const hipStream_t s = (hipStream_t)hip_stream;
-  for (int a = 0; a < d->ndim && e == hipSuccess; ++a) e = launch_plan_tables(&pl[a], (double2*)(base + tw_off[a]), s, true);
+  if (d->ndim == 2) pl[2].n = 0;
+  e = launch_plan_tables(pl, (double2*)base, s, true);
   if (d->ndim == 2) pl[2] = pl[1];
   const int matcode = material_code(d);
   if (e == hipSuccess) e = set_smem_limits(g, matcode, L.smem_max);

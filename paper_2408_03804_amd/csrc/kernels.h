@@ -140,10 +140,14 @@ bool factorize(int n, int* radix, int* nst);
 // complex entries of an axis plan's device tables: twiddles of lds_len, then chirp (n) and filter (m)
 // of a chirp-z axis, or the operand fragments of a dense axis
 size_t plan_table_elems(const AxisPlan& pl);
-// set the table pointers of pl into `base` (plan_table_elems entries, device memory) and fill the
-// tables: the twiddles (exp(-2 pi i j / L) by sincospi of exact rational arguments) unless the
-// caller wrote them there, the chirp-z tables of a chirp-z plan
-hipError_t launch_plan_tables(AxisPlan* pl, double2* base, hipStream_t s, bool twiddles);
+// entries from one axis's tables to the next one's where a grid's axes share a buffer (whole 256 bytes)
+inline size_t plan_table_stride(const AxisPlan& pl) { return (plan_table_elems(pl) + 15) / 16 * 16; }
+// Set the table pointers of the plan pl into `base` (plan_table_elems entries, device memory) and make the
+// tables that the caller's twiddles (exp(-2 pi i j / L), already there) do not cover: a chirp-z plan's, a
+// dense plan's fragments.  all: pl is a grid's three axes (n = 0: none), plan_table_stride entries each,
+// and the twiddles are made too (by sincospi of exact rational arguments; a dense axis gets none, its
+// transform reads the fragments alone): one launch for all axes, beside one for each chirp-z axis.
+hipError_t launch_plan_tables(AxisPlan* pl, double2* base, hipStream_t s, bool all);
 
 hipError_t launch_xfwd(int prod, int mat, const XFwdArgs& a, int B, hipStream_t s);
 hipError_t launch_xinv(int cons, const XInvArgs& a, int B, hipStream_t s);

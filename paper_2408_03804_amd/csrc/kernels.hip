@@ -320,36 +320,53 @@ __global__ void __launch_bounds__(kThreads) k_simp_gradient(const double* F, con
 }
 
 // scale[v] = density[v]^p (SIMP interpolation of the Lame parameters)
-// tw[m] = exp(-2 pi i m / n), m < n (twiddle table of one FFT axis computed on the device)
-__global__ void k_twiddles(double2* tw, int n) {
-  const int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m < n) {
-    double sn, cs;
-    sincospi(2.0 * (double)m / (double)n, &sn, &cs);
-    tw[m] = make_double2(cs, -sn);
-  }
-}
-
-// Operand fragments of the folded dense DFT of length n from its twiddle table tw[m] = exp(-2 pi i m / n):
-// entry (tile, step, lane) holds (cos, sin)(2 pi k t / n) for output row k = 16 tile + lane mod 16 and
-// folded input t = 1 + 4 step + lane / 16, zero past n / 2, and half of it at t = n / 2, whose folded
-// sum counts the same element twice.
-__global__ void k_dense_frags(const double2* tw, int n, double2* frag) {
+// Operand fragments of the folded dense DFT of length n: entry i = (tile, step, lane) holds
+// (cos, sin)(2 pi k t / n) for output row k = 16 tile + lane mod 16 and folded input
+// t = 1 + 4 step + lane / 16, zero past n / 2, and half of it at t = n / 2, whose folded sum counts the
+// same element twice.  From the twiddle table tw[m] = exp(-2 pi i m / n), or (null) by sincospi.
+__device__ __forceinline__ double2 dense_frag(const double2* tw, int n, int i) {
   const int T = n / 2;
   const int steps = dense_steps(n);
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= dense_rows(n) * steps * 64) return;
   const int lane = i & 63;
   const int js = i >> 6;
   const int k = 16 * (js / steps) + (lane & 15);
   const int t = 1 + 4 * (js % steps) + (lane >> 4);
-  double2 v = make_double2(0.0, 0.0);
-  if (k <= T && t <= T) {
-    const double2 w = tw[(k * t) % n];
-    const double h = 2 * t == n ? 0.5 : 1.0;
-    v = make_double2(h * w.x, -h * w.y);
+  if (k > T || t > T) return make_double2(0.0, 0.0);
+  const int m = (k * t) % n;
+  const double h = 2 * t == n ? 0.5 : 1.0;
+  if (tw != nullptr) return make_double2(h * tw[m].x, -h * tw[m].y);
+  double sn, cs;
+  sincospi(2.0 * (double)m / (double)n, &sn, &cs);
+  return make_double2(h * cs, h * sn);
+}
+__global__ void k_dense_frags(const double2* tw, int n, double2* frag) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < dense_rows(n) * dense_steps(n) * 64) frag[i] = dense_frag(tw, n, i);
+}
+
+// The tables of a call that makes them itself, one launch for all axes (axis blockIdx.y): the fragments of
+// a dense axis, which reads nothing else, or the twiddles tw[m] = exp(-2 pi i m / n), m < n, of the stages.
+// Launches of their own for an axis's twiddles and its fragments were six in front of the five passes of a
+// projection, each waiting for the last: 36^3 small strain 57.9 us a call, now 49.2 (radix stages with a
+// launch per axis 51.6); 8^3 29.6 to 25.3.
+struct AxisTables {
+  double2* out[3];
+  int n[3];
+  int count[3];
+  int dense[3];
+};
+__global__ void k_axis_tables(AxisTables a) {
+  const int ax = blockIdx.y;
+  const int n = a.n[ax];
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.count[ax]) return;
+  if (a.dense[ax]) {
+    a.out[ax][i] = dense_frag(nullptr, n, i);
+  } else {
+    double sn, cs;
+    sincospi(2.0 * (double)i / (double)n, &sn, &cs);
+    a.out[ax][i] = make_double2(cs, -sn);
   }
-  frag[i] = v;
 }
 
 // Chirp-z tables of an axis of length n with convolution length m (one block per filter bin k):
@@ -641,28 +658,45 @@ hipError_t launch_simp_gradient(int mat, const double* F, const double* x, MatPa
   return hipGetLastError();
 }
 
-hipError_t launch_plan_tables(AxisPlan* pl, double2* base, hipStream_t s, bool twiddles) {
+// table pointers of pl into base; chirp-z tables on the device
+static void set_tables(AxisPlan* pl, double2* base) {
   const int L = lds_len(*pl);
   pl->tw = base;
   pl->chirp = pl->m > 0 ? base + L : nullptr;
   pl->filt = pl->m > 0 ? base + L + pl->n : nullptr;
-  hipError_t e = hipSuccess;
-  if (twiddles) {
-    hipLaunchKernelGGL(k_twiddles, dim3((unsigned)((L + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, base, L);
-    e = hipGetLastError();
-  }
-  if (pl->dense) {
+  pl->frag = pl->dense ? base + L : nullptr;
+}
+static hipError_t launch_chirp_tables(const AxisPlan& pl, hipStream_t s) {
+  if (pl.m == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_chirp_tables, dim3((unsigned)pl.m), dim3(kThreads), 0, s, const_cast<double2*>(pl.chirp),
+                     const_cast<double2*>(pl.filt), pl.n, pl.m);
+  return hipGetLastError();
+}
+
+hipError_t launch_plan_tables(AxisPlan* pl, double2* base, hipStream_t s, bool all) {
+  if (!all) {
+    set_tables(pl, base);
+    if (!pl->dense) return launch_chirp_tables(*pl, s);
     const int cnt = (int)dense_elems(pl->n);
-    pl->frag = base + L;
     hipLaunchKernelGGL(k_dense_frags, dim3((unsigned)((cnt + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, base, pl->n,
-                       base + L);
-    return e == hipSuccess ? hipGetLastError() : e;
+                       base + lds_len(*pl));
+    return hipGetLastError();
   }
-  if (e == hipSuccess && pl->m > 0) {
-    hipLaunchKernelGGL(k_chirp_tables, dim3((unsigned)pl->m), dim3(kThreads), 0, s, base + L, base + L + pl->n, pl->n,
-                       pl->m);
-    e = hipGetLastError();
+  AxisTables t;
+  int axes = 0, most = 0;
+  for (; axes < 3 && pl[axes].n > 0; ++axes) {
+    AxisPlan& p = pl[axes];
+    set_tables(&p, base);
+    t.out[axes] = p.dense ? base + lds_len(p) : base;
+    t.n[axes] = lds_len(p);
+    t.count[axes] = p.dense ? (int)dense_elems(p.n) : lds_len(p);
+    t.dense[axes] = p.dense;
+    most = std::max(most, t.count[axes]);
+    base += plan_table_stride(p);
   }
+  hipLaunchKernelGGL(k_axis_tables, dim3((unsigned)((most + kThreads - 1) / kThreads), axes), dim3(kThreads), 0, s, t);
+  hipError_t e = hipGetLastError();
+  for (int a = 0; a < axes && e == hipSuccess; ++a) e = launch_chirp_tables(pl[a], s);
   return e;
 }
 
