@@ -67,9 +67,11 @@ enum PlanSet { PLANS_DIRECT = 0, PLANS_CHIRP = 1, PLANS_DENSE = 2 };
 
 // FFT plans of the axes of d (pl[2] = pl[1] in 2D) and the LDS lengths of g that follow from them.
 bool make_plans(const fft_homog_desc* d, int plans, AxisPlan* pl, Geom* g) {
+  long long voxels = 1;
+  for (int a = 0; a < d->ndim; ++a) voxels *= d->n[a];
   for (int a = 0; a < 3; ++a) {
     const int n = a < d->ndim ? d->n[a] : 1;
-    const bool dense = plans >= PLANS_DENSE && dense_len(n, d->ndim);
+    const bool dense = plans >= PLANS_DENSE && dense_len(n, d->ndim, a, d->kinematics == FFT_HOMOG_SMALL_STRAIN, voxels);
     const int lim = plans < PLANS_CHIRP || dense ? 0 : a == d->ndim - 1 ? kChirpOuter : kChirpRows;
     if (!make_plan(n, &pl[a], lim)) return false;
     pl[a].dense = dense ? 1 : 0;

@@ -123,15 +123,32 @@ bool inplace_ok(const AxisPlan& pl, int nseq);
 // length when the direct stages' prime lengths other than 2, 3 and 5 sum to more than chirp_above
 // (0: never); table pointers left null.  False if n has no factorisation within kMaxStages stages.
 bool make_plan(int n, AxisPlan* pl, int chirp_above);
-// true if an axis of length n of a grid of ndim dimensions runs the folded dense DFT: lengths without a
-// compiled schedule from 17 (below, one row tile would be mostly padding) to kDenseMax points, beyond
-// kDenseAll only with a large prime factor.  Measured against the radix and direct prime stages, us per
-// CG iteration (finite strain): 33^3 80 against 97, 57^3 114 / 161, 91^3 298 / 402, 119^3 616 / 864,
-// 119^2 54 / 56; but 143^2 (11 x 13) 68 / 58, 221^2 80 / 63, 143^3 1638 / 1545, as its cost per element
-// grows with n.  In 2D it is even at a prime of 151 and loses at 89 (178^2 75 / 68).
+// true if axis `axis` (0: x), of length n, of a grid of ndim dimensions and `voxels` points runs the folded
+// dense DFT: lengths without a compiled schedule from 17 (below, one row tile would be mostly padding) to
+// kDenseMax points, beyond kDenseAll only with a large prime factor.  Measured against the radix and direct
+// prime stages, us per CG iteration (finite strain): 33^3 80 against 97, 57^3 114 / 161, 91^3 298 / 402,
+// 119^3 616 / 864, 119^2 54 / 56; but 143^2 (11 x 13) 68 / 58, 221^2 80 / 63, 143^3 1638 / 1545, as its cost
+// per element grows with n.  In 2D it is even at a prime of 151 and loses at 89 (178^2 75 / 68).
+// Lengths with no prime factor above 5 have cheap radix stages (two to four).  Their chain of LDS round
+// trips is the longer one where a pass is latency (2D: 36^2 to 125^2 49 / 55 to 60 / 65; 3D up to 30 points:
+// 30^3 71 / 119, 24 cells of 20^3 to 30^3 even), but the dense DFT has more to compute where the card is
+// full.  In 3D
+// - beyond kDenseSmooth points they run the stages (finite strain 72^3 203 / 180, 100^3 418 / 350, 125^3
+//   656 / 520; small strain 72^3 178 / 128, 108^3 449 / 280), except for the finite-strain y passes, three
+//   transforms in a row per block, of at most kDenseFewVoxels (16 x 72 x 16 77 / 84, 16 x 125 x 16 86 / 97,
+//   32 x 125 x 32 112 / 116; 64 x 72 x 64 135 / 130);
+// - in small strain the y axis (whose passes are plain copies through the transform) runs the stages from 36
+//   points on (16 x 36 x 16 66 / 64, 24 cells of it 367 / 321, 23 cells of 32 x 40 x 32 1223 / 1010), and
+//   40 = 8 x 5 points, two stages, on any axis (40^3 82 / 77, 15 cells of it 1341 / 1024);
+// - the others keep the dense DFT (finite strain 36^3 86 / 110, 60^3 115 / 136; small strain, x passes 36^3
+//   13 / 19, 50^3 17 / 23).
+// The cells of a batch run what one cell of their size runs.
 constexpr int kDenseAll = 128;
 constexpr int kDenseMax = 256;
-bool dense_len(int n, int ndim);
+constexpr int kDenseSmooth = 64;
+constexpr long long kDenseFewVoxels = 1 << 17;
+// by default: whether any grid of that many dimensions runs it on an axis of that length
+bool dense_len(int n, int ndim, int axis = 1, bool small = false, long long voxels = 0);
 size_t dense_elems(int n);  // entries of its operand-fragment table
 // LDS rows per sequence of the x, mid and outer transforms of the plans pl[0..ndim-1]
 void set_lds_lens(Geom* g, const AxisPlan* pl);

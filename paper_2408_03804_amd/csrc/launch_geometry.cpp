@@ -144,11 +144,17 @@ bool make_plan(int n, AxisPlan* pl, int chirp_above) {
   return true;
 }
 
-bool dense_len(int n, int ndim) {
+bool dense_len(int n, int ndim, int axis, bool small, long long voxels) {
   if (n < 17 || n > kDenseMax || fixed_nstages(n) != 0) return false;
-  if (n <= kDenseAll) return true;
   int rad[kMaxStages], ns = 0;
-  return !factorize(n, rad, &ns) || direct_sum(rad, ns) > (ndim == 2 ? 120 : 30);
+  const bool staged = factorize(n, rad, &ns);
+  const int sum = staged ? direct_sum(rad, ns) : 1 << 30;
+  if (ndim == 3 && sum == 0 && n > 30) {
+    if (small && (axis == 1 || ns <= 2)) return false;
+    if (n > kDenseSmooth && (small || axis != 1 || voxels > kDenseFewVoxels)) return false;
+  }
+  if (n <= kDenseAll) return true;
+  return sum > (ndim == 2 ? 120 : 30);
 }
 size_t dense_elems(int n) { return (size_t)dense_rows(n) * dense_steps(n) * 64; }
 

@@ -1,0 +1,31 @@
+"""Which transform the axes of a grid run (CPU only)."""
+
+import pytest
+
+from paper_2408_03804_amd import binding
+
+
+def plans(shape, kin="small", cells=1):
+    mat = "linear_elastic" if kin == "small" else "neo_hookean"
+    return binding.fft_homog_debug_axis_plans(binding.make_desc(shape, kin, mat, 2, tangent=cells > 1, batch=cells))
+
+
+@pytest.mark.parametrize("n", [36, 40, 45, 50, 54, 60, 72, 75, 81, 90, 100, 108, 120, 125])
+def test_lengths_with_cheap_radix_stages_leave_the_dense_dft_where_they_are_faster(n):
+    """No prime factor above 5: beyond 64 points in 3D (finite strain: y passes of small grids keep it), and
+    in small strain on the y axis and at 40 points."""
+    d, r = "dense", "direct"
+    assert plans((n, n)) == plans((n, n), "finite") == (d, d)
+    assert plans((n, n, n), "finite") == ((r, r, r) if n > 64 else (d, d, d))
+    small = (r, r, r) if n > 64 or n == 40 else (d, r, d)
+    assert plans((n, n, n)) == small
+    assert plans((16, n, 20)) == ("direct", r, d) and plans((16, n, 20), "finite") == ("direct", d, d)
+    assert plans((48, n, 64), "finite") == ("direct", r if n > 64 else d, "direct")
+    # a cell of a batch runs the transforms it runs alone
+    assert plans((n, n, n), cells=8) == small and plans((n, n, n), "finite", cells=8) == plans((n, n, n), "finite")
+
+
+@pytest.mark.parametrize("n", [17, 18, 20, 24, 25, 27, 30, 33, 35, 49, 63, 65, 66, 77, 91, 104, 126])
+def test_short_lengths_and_those_with_other_primes_run_the_dense_dft(n):
+    for shape in ((n, n), (n, n, n)):
+        assert set(plans(shape)) == set(plans(shape, "finite")) == {"dense"}
