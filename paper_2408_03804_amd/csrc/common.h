@@ -40,6 +40,13 @@ struct FastDiv {
 };
 __host__ __device__ inline FastDiv make_fastdiv(unsigned d) { return FastDiv{d, d > 1 ? 0xFFFFFFFFu / d + 1u : 0u}; }
 
+// Block `lin` of `tot`, dealt round-robin to 8 XCDs, becomes this block of an order in which every XCD's
+// blocks are consecutive (XCD i has tot / 8 of them, one more if i < tot mod 8).
+__host__ __device__ inline unsigned xcd_order(unsigned lin, unsigned tot) {
+  const unsigned xcd = lin & 7u, more = tot & 7u;
+  return xcd * (tot >> 3) + (xcd < more ? xcd : more) + (lin >> 3);
+}
+
 // register-staged FFT stages hold at most this many elements per thread
 constexpr int kInplaceElems = 16;
 

@@ -1,8 +1,29 @@
-"""Which transform the axes of a grid run (CPU only)."""
+"""Launch geometry under the sanitizers, and which transform the axes of a grid run (CPU only)."""
+
+import os
+import subprocess
 
 import pytest
 
 from paper_2408_03804_amd import binding
+from test_host_sanitized import CSRC, ROOT, clangxx
+
+
+@pytest.mark.slow
+def test_launch_geometry_under_sanitizers(tmp_path):
+    cc = clangxx()
+    if cc is None or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("ROCm clang++ and HIP headers not available")
+    exe = str(tmp_path / "plan_driver")
+    cmd = [cc, "-x", "c++", "-std=c++17", "-O1", "-g", "-fno-omit-frame-pointer", "-D__HIP_PLATFORM_AMD__",
+           "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-I/opt/rocm/include",
+           "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, os.path.join(CSRC, "launch_geometry.cpp"),
+           os.path.join(ROOT, "tests", "sanitize", "plan_driver.cpp"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-4000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600,
+                       env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0", UBSAN_OPTIONS="print_stacktrace=1"))
+    assert r.returncode == 0 and " 0 failures" in r.stdout, (r.stdout + r.stderr)[-4000:]
 
 
 def plans(shape, kin="small", cells=1):
