@@ -237,6 +237,12 @@ hipError_t set_smem_limits_dense(const Geom& g, size_t bytes);
 // lengths that have them; each launcher sets *done when it launched (else the caller launches the
 // generic kernel)
 bool fixed_len_kernels(int n);
+// of those (and 128), lengths whose x pass of the CG on displacements has its own kernel with the stored
+// tangent too.  That pass holds both transforms: on the run-time radix stages 32^3 ran slower than on strain
+// fields, whose inverse pass has its own kernels (J2, us per solve, strain fields / run-time stages / own
+// kernel: 32^3 5513 / 5612 / 5459, 64^3 12424 / 10041 / 9633).  Nine components and 96 points spill in four
+// waves: 96^3 Neo-Hookean 102.7 ms on the run-time stages, 105.0 with a kernel of its own; 128^3 192.5 / 190.7.
+constexpr bool stored_len_kernels(int n, bool small) { return small || n <= 64; }
 hipError_t launch_xinv_fixed(int cons, const XInvArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done);
 hipError_t launch_mid_fixed(int dir, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done);
 hipError_t launch_outer_fixed(int mode, bool rows, const AxisArgs& a, dim3 grid, size_t sm, hipStream_t s, bool* done);

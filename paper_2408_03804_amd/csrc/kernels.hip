@@ -448,7 +448,8 @@ hipError_t launch_xfwd(int prod, int mat, const XFwdArgs& a, int B, hipStream_t 
   dim3 grid(nblk_rows(a.g, a.R), B);
   const bool xop = prod == PROD_XOP || prod == PROD_XOP_STORED;
   const size_t sm = xop ? xop_smem(a.g, a.R, a.inplace) : xfwd_smem(a.g, a.R, a.inplace);
-  const bool own = prod == PROD_CGOP || prod == PROD_XOP;  // producers with length-specific kernels
+  // producers with length-specific kernels
+  const bool own = prod == PROD_CGOP || prod == PROD_XOP || (prod == PROD_XOP_STORED && stored_len_kernels(a.px.n, a.g.small));
   int nf = 0;
   if (a.px.dense) nf = kDense;
   else if (a.px.m > 0) nf = kChirp;

@@ -34,6 +34,12 @@ hipError_t xfwd_one(int prod, const XFwdArgs& a, dim3 grid, size_t sm, hipStream
 // 3D axes of a length with its own CG-loop kernels
 template <int MAT, int NF>
 hipError_t xfwd_fixed(int prod, const XFwdArgs& a, dim3 grid, size_t sm, hipStream_t s) {
+  if constexpr (stored_len_kernels(variant_len(NF), !finite_mat(MAT))) {
+    if (prod == PROD_XOP_STORED) {
+      hipLaunchKernelGGL((k_xop<1, MAT, 3, NF>), grid, dim3(kThreads), sm, s, a);
+      return hipGetLastError();
+    }
+  }
   if (prod == PROD_XOP) hipLaunchKernelGGL((k_xop<0, MAT, 3, NF>), grid, dim3(kThreads), sm, s, a);
   else if (prod == PROD_CGOP) hipLaunchKernelGGL((k_xfwd<PROD_CGOP, MAT, 3, NF>), grid, dim3(kThreads), sm, s, a);
   else return hipErrorInvalidValue;
@@ -79,6 +85,12 @@ hipError_t limits_one(size_t bytes) {
   return e;
 }
 
+template <int MAT, int NF>
+hipError_t stored_limit(size_t bytes) {
+  if constexpr (stored_len_kernels(variant_len(NF), !finite_mat(MAT))) return raise_limit(k_xop<1, MAT, 3, NF>, bytes);
+  return hipSuccess;
+}
+
 template <int MAT, int NDIM>
 hipError_t limits_all(size_t bytes) {
   hipError_t e = limits_one<MAT, NDIM, 0>(bytes);
@@ -96,6 +108,11 @@ hipError_t limits_all(size_t bytes) {
                            reinterpret_cast<const void*>(k_xop<0, MAT, 3, kStaged + 48>),
                            reinterpret_cast<const void*>(k_xop<0, MAT, 3, kStaged + 32>)})
       if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) e = stored_limit<MAT, 128>(bytes);
+    if (e == hipSuccess) e = stored_limit<MAT, kStaged + 96>(bytes);
+    if (e == hipSuccess) e = stored_limit<MAT, kStaged + 64>(bytes);
+    if (e == hipSuccess) e = stored_limit<MAT, kStaged + 48>(bytes);
+    if (e == hipSuccess) e = stored_limit<MAT, kStaged + 32>(bytes);
   }
   return e;
 }
