@@ -107,13 +107,15 @@ typedef struct fft_homog_desc {
   int ndim;          /* 2 or 3 */
   int n[3];          /* grid points along x, y, z; each 1..1024.  Lengths with a compiled schedule run
                         its radix stages.  Others of 17..128 run a folded dense DFT on the matrix
-                        cores, and so do those of 129..256 whose prime factors above 5 add up to more
-                        than 120 (2D) or 30 (3D).  The rest run radix stages for factors 2, 3, 5 and a
-                        direct DFT stage for each other prime factor, or, when those add up to more
-                        than 270 (outer axis) or 410 (x and y axes), the chirp-z (Bluestein)
-                        transform through cyclic convolutions of a length m >= 2n - 1 with factors 2,
-                        3, 5.  If the buffers of the dense DFT or of the chirp-z form do not fit, no
-                        axis runs it */
+                        cores, except, in 3D, those with factors 2, 3, 5 only where the stages are
+                        faster (beyond 64 points, and some from 36 on), and so do those of 129..256
+                        whose prime factors above 5 add up to more than 120 (2D) or 85 (3D).  The rest
+                        run radix stages for factors 2, 3, 5 and a direct DFT stage for each other
+                        prime factor, or, when those add up to more than 270 (outer axis) or 410 (x
+                        and y axes), the chirp-z (Bluestein) transform through cyclic convolutions of
+                        a length m >= 2n - 1 with factors 2, 3, 5.  If the buffers of the dense DFT
+                        or of the chirp-z form do not fit, no axis runs it.
+                        fft_homog_debug_axis_plans tells */
   double len[3];     /* cell edge lengths along x, y, z (> 0); wavevector xi = 2 pi k / len */
   int kinematics;    /* FFT_HOMOG_SMALL_STRAIN or FFT_HOMOG_FINITE_STRAIN */
   int material;      /* LINEAR_ELASTIC or J2_PLASTIC (small), NEO_HOOKEAN or STVK (finite); J2

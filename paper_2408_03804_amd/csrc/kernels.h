@@ -128,7 +128,13 @@ bool make_plan(int n, AxisPlan* pl, int chirp_above);
 // kDenseMax points, beyond kDenseAll only with a large prime factor.  Measured against the radix and direct
 // prime stages, us per CG iteration (finite strain): 33^3 80 against 97, 57^3 114 / 161, 91^3 298 / 402,
 // 119^3 616 / 864, 119^2 54 / 56; but 143^2 (11 x 13) 68 / 58, 221^2 80 / 63, 143^3 1638 / 1545, as its cost
-// per element grows with n.  In 2D it is even at a prime of 151 and loses at 89 (178^2 75 / 68).
+// per element grows with n.  The line beyond kDenseAll is on the sum of the primes above 5.  2D: 120; even at
+// a prime of 151, 178^2 (89) 75 / 68.  3D: 85; one long axis over 96 x 96, us per iteration of the stages over
+// the dense DFT's, small strain x, y, outer axis and finite strain the same: 161 (7 x 23) 0.91 0.82 1.00, 0.92
+// 0.91 1.01; 164 (41) 0.86 0.76 0.92, 0.86 0.87 0.95; 201 (67) 1.10 0.97 0.99, 0.88 1.10 0.94; 237 (79) 1.12
+// 1.03 1.02, 0.97 1.19 1.19; 178 (89) 1.30 1.05 1.10, 1.06 1.32 1.10; 254 (127) 1.30 1.19 1.17, 1.15 1.41
+// 1.33.  (Over 24 x 24, where a pass is latency, the stages gain below the line too: 0.83 to 1.06 at 41 to 79,
+// the finite-strain y axis 0.6.)
 // Lengths with no prime factor above 5 have cheap radix stages (two to four).  Their chain of LDS round
 // trips is the longer one where a pass is latency (2D: 36^2 to 125^2 49 / 55 to 60 / 65; 3D up to 30 points:
 // 30^3 71 / 119, 24 cells of 20^3 to 30^3 even), but the dense DFT has more to compute where the card is

@@ -154,7 +154,7 @@ bool dense_len(int n, int ndim, int axis, bool small, long long voxels) {
     if (n > kDenseSmooth && (small || axis != 1 || voxels > kDenseFewVoxels)) return false;
   }
   if (n <= kDenseAll) return true;
-  return sum > (ndim == 2 ? 120 : 30);
+  return sum > (ndim == 2 ? 120 : 85);
 }
 size_t dense_elems(int n) { return (size_t)dense_rows(n) * dense_steps(n) * 64; }
 

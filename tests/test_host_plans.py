@@ -50,3 +50,17 @@ def test_lengths_with_cheap_radix_stages_leave_the_dense_dft_where_they_are_fast
 def test_short_lengths_and_those_with_other_primes_run_the_dense_dft(n):
     for shape in ((n, n), (n, n, n)):
         assert set(plans(shape)) == set(plans(shape, "finite")) == {"dense"}
+
+
+@pytest.mark.parametrize("n,two,three", [(143, "direct", "direct"), (155, "direct", "direct"), (161, "direct", "direct"),
+                                         (164, "direct", "direct"), (201, "direct", "direct"), (237, "direct", "direct"),
+                                         (178, "direct", "dense"), (218, "direct", "dense"), (254, "dense", "dense"),
+                                         (131, "dense", "dense"), (199, "dense", "dense"), (251, "dense", "dense"),
+                                         (257, "direct", "direct")])
+def test_longer_lengths_run_the_dense_dft_for_large_primes(n, two, three):
+    """Sum of the primes above 5: more than 120 in 2D, 85 in 3D."""
+    assert plans((n, 8)) == (two, "direct") and plans((8, n), "finite") == ("direct", two)
+    for i in range(3):
+        shape = tuple(n if a == i else 8 for a in range(3))
+        for kin in ("small", "finite"):
+            assert plans(shape, kin) == tuple(three if a == i else "direct" for a in range(3))
