@@ -112,8 +112,9 @@ typedef struct fft_homog_desc {
                         whose prime factors above 5 add up to more than 120 (2D) or 85 (3D).  The rest
                         run radix stages for factors 2, 3, 5 and a direct DFT stage for each other
                         prime factor, or, when those add up to more than 270 (outer axis) or 410 (x
-                        and y axes), the chirp-z (Bluestein) transform through cyclic convolutions of
-                        a length m >= 2n - 1 with factors 2, 3, 5.  If the buffers of the dense DFT
+                        and y axes; up to 400 points 360, in 3D finite strain 300), the chirp-z
+                        (Bluestein) transform through cyclic convolutions of a length m >= 2n - 1
+                        with factors 2, 3, 5.  If the buffers of the dense DFT
                         or of the chirp-z form do not fit, no axis runs it.
                         fft_homog_debug_axis_plans tells */
   double len[3];     /* cell edge lengths along x, y, z (> 0); wavevector xi = 2 pi k / len */

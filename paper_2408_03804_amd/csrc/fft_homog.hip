@@ -53,26 +53,19 @@ struct Layout {
   int plans;  // which transforms the axes may take (PlanSet)
 };
 
-// Chirp-z thresholds (sum of the direct stages' prime lengths above 5, see make_plan), measured per
-// pass from CG-iteration kernel times of n x n grids with both forms, direct against chirp-z in us:
-// the outer pass (G-hat between a forward and an inverse transform) 37 / 58 at 107 (321 = 3 * 107),
-// 48 / 55 at 257, 54 / 52 at 283 and 57 / 50 at 307; the two x passes together 68 / 93 at 199,
-// 103 / 108 at 401, 108 / 104 at 439 and 123 / 101 at 499.
-constexpr int kChirpOuter = 270;
-constexpr int kChirpRows = 410;
-
 // Transforms the axes of a layout may take: radix and direct prime stages only, also the chirp-z
 // form, also the folded dense DFT.
 enum PlanSet { PLANS_DIRECT = 0, PLANS_CHIRP = 1, PLANS_DENSE = 2 };
 
 // FFT plans of the axes of d (pl[2] = pl[1] in 2D) and the LDS lengths of g that follow from them.
 bool make_plans(const fft_homog_desc* d, int plans, AxisPlan* pl, Geom* g) {
+  const bool small = d->kinematics == FFT_HOMOG_SMALL_STRAIN;
   long long voxels = 1;
   for (int a = 0; a < d->ndim; ++a) voxels *= d->n[a];
   for (int a = 0; a < 3; ++a) {
     const int n = a < d->ndim ? d->n[a] : 1;
-    const bool dense = plans >= PLANS_DENSE && dense_len(n, d->ndim, a, d->kinematics == FFT_HOMOG_SMALL_STRAIN, voxels);
-    const int lim = plans < PLANS_CHIRP || dense ? 0 : a == d->ndim - 1 ? kChirpOuter : kChirpRows;
+    const bool dense = plans >= PLANS_DENSE && dense_len(n, d->ndim, a, small, voxels);
+    const int lim = plans < PLANS_CHIRP || dense ? 0 : chirp_limit(n, d->ndim, a, small);
     if (!make_plan(n, &pl[a], lim)) return false;
     pl[a].dense = dense ? 1 : 0;
   }

@@ -123,6 +123,26 @@ bool inplace_ok(const AxisPlan& pl, int nseq);
 // length when the direct stages' prime lengths other than 2, 3 and 5 sum to more than chirp_above
 // (0: never); table pointers left null.  False if n has no factorisation within kMaxStages stages.
 bool make_plan(int n, AxisPlan* pl, int chirp_above);
+// chirp_above of axis `axis` (0: x) of length n.  Measured per pass (us per CG iteration, direct stages / chirp-z;
+// the outer pass, both directions, and the x or y passes together) on n x n grids and on one long axis over
+// 64 x 64.  The chirp-z form's cost is that of its length m, the direct stages' grows with the prime.
+// Outer axis, 270: 2D 257 48 / 55, 311 55 / 46; 3D finite strain 257 348 / 485, 311 512 / 470, 433 939 / 727,
+// small strain 311 542 / 508.  (Two lengths between are not in line, for m has five radix stages there or two
+// blocks no longer fit a CU: 337 559 / 628 and 586 / 941, 401 710 / 772 and 832 / 1129.)
+// x and y, up to 400 points (m <= 800), 300 in 3D finite strain: x 257 500 / 628, 311 672 / 609, 337 888 / 717,
+// 379 1002 / 651, y 257 626 / 665, 311 774 / 677, 379 1067 / 761; 360 elsewhere: small strain x 311 425 / 453,
+// 337 457 / 518, 379 575 / 498, y 337 504 / 568, 379 580 / 515, 2D x 337 88 / 94, 379 97 / 88.
+// Longer ones, whose buffers leave fewer blocks on a CU, 410: finite strain x 401 1076 / 1490, y 401 1229 / 1141,
+// 433 1495 / 1093; small strain x 401 657 / 644, 433 750 / 607, y 401 681 / 806, 433 807 / 780; 2D 401 102 / 107,
+// 433 108 / 103.
+constexpr int kChirpOuter = 270;
+constexpr int kChirpRowsFinite = 300;
+constexpr int kChirpRowsShort = 360;
+constexpr int kChirpRows = 410;
+inline int chirp_limit(int n, int ndim, int axis, bool small) {
+  if (axis == ndim - 1) return kChirpOuter;
+  return n > 400 ? kChirpRows : ndim == 3 && !small ? kChirpRowsFinite : kChirpRowsShort;
+}
 // true if axis `axis` (0: x), of length n, of a grid of ndim dimensions and `voxels` points runs the folded
 // dense DFT: lengths without a compiled schedule from 17 (below, one row tile would be mostly padding) to
 // kDenseMax points, beyond kDenseAll only with a large prime factor.  Measured against the radix and direct

@@ -1,8 +1,8 @@
 """The chirp-z transform on every axis of every pass that can run it.
 
 Each case names the transform its axes take, so that a change of the rule that moves a length elsewhere
-fails here and does not empty the test.  Lengths: primes above the limits of the direct stages, with the
-smallest convolution lengths, so that the buffers of all components fit.  Bounds are those of the same
+fails here and does not empty the test.  Lengths: primes above the limits of the direct stages, short
+enough that the buffers of all components fit.  Bounds are those of the same
 checks on other axes: 1e-13 for one projection, operator or transform, 1e-10 (fields) and 1e-11
 (homogenized) for solves; at a CG tolerance of 1e-11 the passes are those of the CG on displacements, at
 1e-12 those of the CG on strain fields.
@@ -24,6 +24,7 @@ D, C = "direct", "chirp"
 CASES = [((4, 433, 6), "small", (D, C, D)), ((4, 433, 6), "finite", (D, C, D)),
          ((283, 5, 4), "small", (C, D, D)), ((307, 4, 5), "finite", (C, D, D)), ((433, 3, 4), "finite", (C, D, D)),
          ((3, 4, 433), "small", (D, D, C)),
+         ((4, 311, 6), "finite", (D, C, D)), ((3, 2, 379), "finite", (D, D, C)), ((4, 379, 3), "small", (D, C, D)), ((5, 379), "small", (D, C)),
          ((6, 433), "small", (D, C)), ((433, 6), "finite", (C, D)), ((5, 439), "finite", (D, C)), ((283, 433), "small", (C, C))]
 IDS = ["%s-%s" % ("x".join(map(str, s)), k) for s, k, _ in CASES]
 

@@ -64,3 +64,20 @@ def test_longer_lengths_run_the_dense_dft_for_large_primes(n, two, three):
         shape = tuple(n if a == i else 8 for a in range(3))
         for kin in ("small", "finite"):
             assert plans(shape, kin) == tuple(three if a == i else "direct" for a in range(3))
+
+
+@pytest.mark.parametrize("n,two,small,finite", [(257, "direct", "direct", "direct"), (311, "direct", "direct", "chirp"),
+                                                (337, "direct", "direct", "chirp"), (379, "chirp", "chirp", "chirp"),
+                                                (358, "direct", "direct", "direct"), (401, "direct", "direct", "direct")])
+def test_x_and_y_axes_run_chirp_z_for_large_primes(n, two, small, finite):
+    """Sum of the primes above 5: up to 400 points more than 300 (3D finite strain) or 360, beyond more than 410."""
+    assert plans((8, n)) == plans((8, n), "finite") == ("direct", two)
+    assert plans((8, n, 6)) == ("direct", small, "direct") and plans((8, 6, n)) == ("direct", "direct", small)
+    assert plans((8, n, 6), "finite") == ("direct", finite, "direct")
+    assert plans((8, 6, n), "finite") == ("direct", "direct", finite)
+
+
+def test_outer_axes_run_chirp_z_for_large_primes():
+    for n, kind in ((257, "direct"), (283, "chirp"), (311, "chirp")):
+        for kin in ("small", "finite"):
+            assert plans((n, 8), kin) == (kind, "direct") and plans((n, 6, 8), kin) == (kind, "direct", "direct")
