@@ -470,8 +470,8 @@ AxisArgs cg_outer_args(fft_homog_t* h, int TX, int inplace = -1) {
   a.stream = bytes > 256e6 && TX % 8 == 0 && h->g.nxp % 8 == 0;
   return a;
 }
-AxisArgs cg_mid_args(fft_homog_t* h, const CgState* st, bool alpha) {
-  AxisArgs a = axis_args(h, 1, h->L.TXm, st);
+AxisArgs cg_mid_args(fft_homog_t* h, int TX, const CgState* st, bool alpha, int inplace = -1) {
+  AxisArgs a = axis_args(h, 1, TX, st, inplace);
   a.mirror = 1;
   if (alpha) {
     a.pq_st = h->st;
@@ -505,7 +505,7 @@ int enqueue_rhs(fft_homog_t* h, int B) {
   FH_CK(launch_cg_reduce(RED_SRC, h->st, h->partials, h->L.nblk_x, B, h->stream));
   if (h->disp) {
     const AxisArgs ao = cg_outer_args(h, h->L.TXo);
-    FH_CK(launch_mid(-1, cg_mid_args(h, nullptr, false), B, h->stream));
+    FH_CK(launch_mid(-1, cg_mid_args(h, h->L.TXm, nullptr, false), B, h->stream));
     FH_CK(launch_outer(OUTER_RHS, ao, B, h->stream));
     FH_CK(launch_cg_reduce(RED_RHS, h->st, h->rr_partials, ao.rr_nblocks, B, h->stream));
     return FFT_HOMOG_OK;
@@ -587,7 +587,7 @@ struct CgLaunches {
         xi(xinv_args(h_)), active(active_) {
     mi = axis_args(h, 1, h->L.TXm, h->st);
     if (disp) {
-      mf = cg_mid_args(h, h->st, true);
+      mf = cg_mid_args(h, h->L.TXm, h->st, true);
       o = cg_outer_args(h, h->L.TXo);
     } else {
       mf = mi;
@@ -1609,11 +1609,14 @@ int fft_homog_autotune(fft_homog_t* h, int reps, int* shape) {
             if ((pass == 0) != incumbent) continue;
             if (ip && !inplace_ok(h->plan[1], mid_sequences(g, t, 1, 1))) continue;
             if (!incumbent && (mid_smem(g, t, ip, 1, 1) > kLdsTune || !mid_fits(g, t, 1, 1))) continue;
-            const AxisArgs a = axis_args(h, 1, t, h->st, ip);
+            // the forward pass with what the CG adds to it (on displacements: the mirror planes, and alpha,
+            // which stays zero: the x pass above left <p, K:p> = 0, so the pass only flags it)
+            const AxisArgs ai = axis_args(h, 1, t, h->st, ip);
+            const AxisArgs af = h->disp ? cg_mid_args(h, t, h->st, true, ip) : ai;
             double ms = 0.0;
             FH_CK(time_launches(h, reps, [&]() {
-              hipError_t e = launch_mid(-1, a, Bt, h->stream);
-              return e == hipSuccess ? launch_mid(1, a, Bt, h->stream) : e;
+              hipError_t e = launch_mid(-1, af, Bt, h->stream);
+              return e == hipSuccess ? launch_mid(1, ai, Bt, h->stream) : e;
             }, &ms));
             if (incumbent) bt = ms;
             else if (ms < kGain * bt) { bt = ms; cur.TXm = t; cur.in_m = ip; }
