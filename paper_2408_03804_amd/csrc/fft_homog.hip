@@ -104,6 +104,9 @@ static int material_code(const fft_homog_desc* d) {
   return 2 * d->material + (d->ndim - 2);
 }
 
+// whether the handle's CG runs on displacements (else on strain fields)
+bool displacement_cg(const fft_homog_desc* d) { return d->ndim == 3 && d->tol_cg >= kDisplacementTol; }
+
 int validate_desc(const fft_homog_desc* d) {
   if (!d) return FFT_HOMOG_EINVAL;
   if (d->ndim != 2 && d->ndim != 3) return FFT_HOMOG_EINVAL;
@@ -236,8 +239,10 @@ int make_layout_with(const fft_homog_desc* d, Layout* L, int plans) {
   };
   const size_t fld = (size_t)C * g.N * sizeof(double);
   L->F = take(fld);
-  // x, r, p: strain fields, or the CG on displacements' half spectra [d][Nh]
-  const size_t vec = std::max<size_t>(fld, (size_t)d->ndim * g.Nh * sizeof(double2)) * L->B;
+  // x, r, p: strain fields (which finish_solution writes in either case), or the CG on displacements' half
+  // spectra [d][Nh]
+  const bool disp = displacement_cg(d);
+  const size_t vec = std::max<size_t>(fld, disp ? (size_t)d->ndim * g.Nh * sizeof(double2) : 0) * L->B;
   L->x = take(vec);
   L->r = take(vec);
   L->p = take(vec);
@@ -262,7 +267,7 @@ int make_layout_with(const fft_homog_desc* d, Layout* L, int plans) {
   L->n_partials = np;
   L->partials = take(np * sizeof(double));
   // <r, r> of the CG on displacements: one partial per outer-pass block, one bin wide at the least
-  L->rr_partials = take((size_t)L->B * g.nxh * g.n_mid * outer_groups_per_rhs(g) * sizeof(double));
+  L->rr_partials = take(disp ? (size_t)L->B * g.nxh * g.n_mid * outer_groups_per_rhs(g) * sizeof(double) : 0);
   L->state = take((size_t)L->B * sizeof(CgState));
   L->active = take((size_t)L->B * sizeof(int));
   L->n_results = std::max((size_t)kResults, (size_t)L->cells * C * C);
@@ -900,7 +905,7 @@ int fft_homog_create(const fft_homog_desc* d, void* dev_workspace, size_t bytes,
   h->table = (double*)(h->ws + L.table);
   h->partials = (double*)(h->ws + L.partials);
   h->rr_partials = (double*)(h->ws + L.rr_partials);
-  h->disp = d->ndim == 3 && d->tol_cg >= kDisplacementTol;
+  h->disp = displacement_cg(d);
   h->st = (CgState*)(h->ws + L.state);
   h->results = (double*)(h->ws + L.results);
   h->flags = (int*)(h->ws + L.flags);
