@@ -163,7 +163,8 @@ __device__ inline int chunk_k(bool kc, int p) {
 // Four chunks of an operand in memory, zero outside [0, nrows) x [.., kend).  VEC: every chunk inside is
 // 16 aligned bytes.  Loads are then unconditional, from a clamped address, and chunks outside are cleared
 // when they are stored (ok): a load under a condition is waited for where its branch ends, not where its
-// value is used, which left nothing in flight during the products.
+// value is used, which left nothing in flight during the products.  Else every chunk decides for itself:
+// 16 bytes where it is whole and aligned, entry by entry otherwise.
 struct Chunks {
   uint4 v[4];
   bool ok[4];
@@ -184,6 +185,10 @@ __device__ inline void fetch_tile(Chunks& f, const bf16* P, long long s_row, lon
       if (!f.ok[p]) continue;
       const bf16* src = P + (long long)row * s_row + (long long)k * s_k;
       const int left = KC ? kend - k : nrows - row;  // entries of the 8 inside
+      if (left >= 8 && (reinterpret_cast<uintptr_t>(src) & 15u) == 0) {
+        f.v[p] = *reinterpret_cast<const uint4*>(src);
+        continue;
+      }
       uint64_t lo = 0, hi = 0;
 #pragma unroll 1
       for (int i = 0; i < min(left, 8); ++i) {
@@ -285,7 +290,8 @@ __device__ inline void store_row4(v4f x, int col, int N, bool wide, const float*
 // on their way to registers while it multiplies this one (two ahead gained nothing).  With one 32-deep
 // step at a time the conv products of 256 cells of 32^3 took, in mean, 67 us (forward, blocks 2-4) and
 // 141 us (weight gradient), now 39 and 51 us; block 1's weight gradient 78, now 50 us.
-template <int AOP, int BOP, bool VEC>
+// VA, VB: VEC of the operand in memory.
+template <int AOP, int BOP, bool VA, bool VB>
 __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(3))) k_gemm(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) bf16 As[BM * BK];
   __shared__ __attribute__((aligned(16))) bf16 Bs[BN * BK];
@@ -324,7 +330,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(3))) k_
         fa.v[p] = conv_gather(arow[p], t);
       }
     } else {
-      fetch_tile<AOP == OP_K, VEC>(fa, g.A, g.sam, g.sak, m0, g.M, k0, kend);
+      fetch_tile<AOP == OP_K, VA>(fa, g.A, g.sam, g.sak, m0, g.M, k0, kend);
     }
     if constexpr (BOP == OP_COLT || BOP == OP_BITS) {
 #pragma unroll
@@ -339,7 +345,7 @@ __global__ void __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(3))) k_
         }
       }
     } else {
-      fetch_tile<BOP == OP_K, VEC>(fb, g.B, g.sbn, g.sbk, n0, g.N, k0, kend);
+      fetch_tile<BOP == OP_K, VB>(fb, g.B, g.sbn, g.sbk, n0, g.N, k0, kend);
     }
   };
   auto put = [&] {
@@ -588,16 +594,21 @@ hipError_t gemm(int M, int N, int K, const bf16* A, long long sam, long long sak
   g.act = act;
   dim3 grid((M + BM - 1) / BM, (N + BN - 1) / BN, S);
   const bool ak = sak == 1, bk = sbk == 1;
-  const bool vec = vector_chunks(A, ak ? sam : sak, ak ? K : M) && vector_chunks(B, bk ? sbn : sbk, bk ? K : N);
-  auto launch = [&](auto v) {
-    constexpr bool VEC = decltype(v)::value;
-    if (ak && bk) hipLaunchKernelGGL((k_gemm<OP_K, OP_K, VEC>), grid, dim3(kT), 0, s, g);
-    else if (ak) hipLaunchKernelGGL((k_gemm<OP_K, OP_ROW, VEC>), grid, dim3(kT), 0, s, g);
-    else if (bk) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_K, VEC>), grid, dim3(kT), 0, s, g);
-    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_ROW, VEC>), grid, dim3(kT), 0, s, g);
+  // each operand by itself: with one ragged operand (the 21 outputs of the last layer, channels that are no
+  // multiple of 8) putting both on the other path made a training step of 12, 28, 52 and 100 channels slower
+  // than with each chunk deciding for itself (1006 us -> 1161, now 847; 30, 60, 120, 240: 1416, now 1284)
+  const bool va = vector_chunks(A, ak ? sam : sak, ak ? K : M), vb = vector_chunks(B, bk ? sbn : sbk, bk ? K : N);
+  auto launch = [&](auto a, auto b) {
+    constexpr bool VA = decltype(a)::value, VB = decltype(b)::value;
+    if (ak && bk) hipLaunchKernelGGL((k_gemm<OP_K, OP_K, VA, VB>), grid, dim3(kT), 0, s, g);
+    else if (ak) hipLaunchKernelGGL((k_gemm<OP_K, OP_ROW, VA, VB>), grid, dim3(kT), 0, s, g);
+    else if (bk) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_K, VA, VB>), grid, dim3(kT), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_ROW, VA, VB>), grid, dim3(kT), 0, s, g);
   };
-  if (vec) launch(std::true_type{});
-  else launch(std::false_type{});
+  if (va && vb) launch(std::true_type{}, std::true_type{});
+  else if (va) launch(std::true_type{}, std::false_type{});
+  else if (vb) launch(std::false_type{}, std::true_type{});
+  else launch(std::false_type{}, std::false_type{});
   return hipGetLastError();
 }
 
@@ -620,7 +631,7 @@ hipError_t gemm_conv_forward(int M, int N, int Kp, const ConvOperand& cv, const 
   g.bias = bias;
   g.act = act;
   g.cv = cv;
-  hipLaunchKernelGGL((k_gemm<OP_COL, OP_K, true>), dim3((M + BM - 1) / BM, (N + BN - 1) / BN, 1), dim3(kT), 0, s, g);
+  hipLaunchKernelGGL((k_gemm<OP_COL, OP_K, true, true>), dim3((M + BM - 1) / BM, (N + BN - 1) / BN, 1), dim3(kT), 0, s, g);
   return hipGetLastError();
 }
 hipError_t gemm_conv_wgrad(int Co, int Kp, int M, const bf16* dpre, const ConvOperand* cv, const uint8_t* bits, float* C,
@@ -640,11 +651,11 @@ hipError_t gemm_conv_wgrad(int Co, int Kp, int M, const bf16* dpre, const ConvOp
   const bool vec = vector_chunks(dpre, Co, Co);
   if (cv) {
     g.cv = *cv;
-    if (vec) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_COLT, true>), grid, dim3(kT), 0, s, g);
-    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_COLT, false>), grid, dim3(kT), 0, s, g);
+    if (vec) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_COLT, true, true>), grid, dim3(kT), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_COLT, false, true>), grid, dim3(kT), 0, s, g);
   } else {
-    if (vec) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_BITS, true>), grid, dim3(kT), 0, s, g);
-    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_BITS, false>), grid, dim3(kT), 0, s, g);
+    if (vec) hipLaunchKernelGGL((k_gemm<OP_ROW, OP_BITS, true, true>), grid, dim3(kT), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm<OP_ROW, OP_BITS, false, true>), grid, dim3(kT), 0, s, g);
   }
   return hipGetLastError();
 }
