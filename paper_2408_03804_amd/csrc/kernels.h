@@ -18,9 +18,16 @@ enum OuterMode {
   OUTER_SOLUTION = 6, OUTER_RESIDUAL = 7
 };
 inline bool outer_cg_mode(int mode) { return mode >= OUTER_CGFWD; }
-// 3D grids with a CG tolerance from here on run the CG on displacements (pass_kernels.h).  A 2D grid has
-// no y pass to save the traffic in, its launches are what an iteration costs: 25.2 ms on strain fields
-// against 27.2 on displacements per solve at 299^2.
+// 3D grids with a CG tolerance from here on run the CG on displacements (pass_kernels.h).  Where the two forms
+// take the same iterations it is the faster one at any tolerance: 33^3, 64^3 and 128^3, contrast 10 and 20,
+// linear elastic, Neo-Hookean, St. Venant-Kirchhoff and J2, at 1e-10 to 1e-13 the counts are equal or one
+// apart (64^3 tangent at contrast 100: equal) and a Neo-Hookean solve takes 22.4 ms against 23.1 at 33^3 (1e-10),
+// 34.3 / 48.4 at 64^3 and 168.8 / 203.4 at 128^3 (both 1e-12).  Where rounding decides the counts they are not
+// those of the textbook CG on strains: 6 x 5 x 7 with densities from 0.05, cubed, 152 / 154 iterations at 1e-11,
+// 164 / 168 at 1e-12, 177 / 184 at 1e-13; 16^3 with densities from 0.01 21556 / 21025 at 1e-12; and a tolerance
+// beyond rounding (16^3, 1e-16) is met by its recursive residual where the strain fields' stagnates.  Callers
+// that ask for less than 1e-11 compare with the textbook iteration and keep it.
+// There is no such form in 2D, which has no y pass to save traffic in and whose iterations cost their launches.
 constexpr double kDisplacementTol = 1e-11;
 enum Reduce { RED_SRC = 0, RED_RHS = 1, RED_PQ = 2, RED_RR = 3 };
 

@@ -36,8 +36,8 @@
 // over the half spectrum, w = 2 except on the planes kx = 0 and kx = nx/2.  These are the iterates of
 // the CG on the strains in exact arithmetic; at 128^3 (finite strain) an iteration moves 731 B per
 // voxel instead of 1064 B.  In floating point the strain fields also carry an incompatible rounding
-// part that no iteration reduces; near that floor (tolerances around 1e-12) it shifts the iteration
-// count by a few per cent, and callers that compare counts there expect those of the textbook CG.
+// part that no iteration reduces; where rounding decides the iteration count (badly conditioned cells) the
+// counts of the two differ by one to four per cent (kDisplacementTol, with the measurements).
 // The spectra of real fields on the planes kx = 0 and kx = nx/2 are Hermitian in the other axes.  A
 // part of r that is not (rounding of the transforms) would vanish on the way through real space and
 // so never be reduced; the forward passes of the CG on displacements therefore keep that symmetry
