@@ -195,7 +195,7 @@ inline size_t plan_table_stride(const AxisPlan& pl) { return (plan_table_elems(p
 // Set the table pointers of the plan pl into `base` (plan_table_elems entries, device memory) and make the
 // tables that the caller's twiddles (exp(-2 pi i j / L), already there) do not cover: a chirp-z plan's, a
 // dense plan's fragments.  all: pl is a grid's three axes (n = 0: none), plan_table_stride entries each,
-// and the twiddles are made too (by sincospi of exact rational arguments; a dense axis gets none, its
+// and the twiddles are made too (by sincospi of reduced arguments; a dense axis gets none, its
 // transform reads the fragments alone): one launch for all axes, beside one for each chirp-z axis.
 hipError_t launch_plan_tables(AxisPlan* pl, double2* base, hipStream_t s, bool all);
 
